@@ -3,8 +3,9 @@
 Step = one call of hwr_route_batch over the whole throughput workload
 (1,048,576 queries x 256 model-GPU pairs, 16 chunks of 65,536 queries on one
 stream, inputs resident in HBM).  Prints one JSON line with candidates
-scored per second, the roofline position of the dominant kernel (the fused
-predictor, MFMA-bound) measured with HIP events on the launch stream, the
+scored per second, the roofline position of the dominant kernel (quality and
+decisions, HBM-bound; in the staged pipeline the predictor, MFMA-bound)
+measured with HIP events on the launch stream, the
 single-query latency path (p50 / p99 over 10,000 sequential calls with a
 state update between calls), and the CPU oracle timed on a bounded sample.
 
@@ -42,8 +43,8 @@ PROFILE_EVERY = 4              # kernel timing samples one launch in four of eac
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_C5_1Mx256.json")
 KERNEL_NAMES = {   # as the profiler names them
-    "fused": "void hwr::k_mlp_bf16<256, false, 2, true, 4, true>(hwr::MlpArgs)",
-    "mlp": "void hwr::k_mlp_bf16<256, true, 2, true, 4, false>(hwr::MlpArgs)",
+    "fused": "void hwr::k_route<true, false, false, false, false>(hwr::RouteArgs)",
+    "mlp": "void hwr::k_mlp_bf16<256, 2, true, 4>(hwr::MlpArgs)",
     "quality": "hwr::k_quality_bf16_lds(hwr::QualityArgs)",
     "gather": "hwr::k_gather(hwr::GatherArgs)",
     "epilogue": "void hwr::k_epilogue<false, false, false, false>(hwr::EpilogueArgs)",
@@ -175,39 +176,44 @@ def throughput(args, hwr, torch, w, pipeline, steps, warmup):
         ms, cnt = kt[k]
         return ms / cnt if cnt else 0.0
 
-    kname = "fused" if pipeline == "fused" else "mlp"
-    k_avg_ms = avg(kname)
     traffic = counter_traffic(args.workload)
     nq = sp.n_queries
     chunk_cands = nq * N
-    flops = predictor_flops(sp.feat_dim, sp.hidden) * chunk_cands
-    achieved = flops / (k_avg_ms / 1e3) / 1e12
-    qflops = 2 * nq * D * M
-    qk_ms = k_avg_ms + avg("quality")
-    with_q = (flops + qflops) / (qk_ms / 1e3) / 1e12 if qk_ms > 0 else 0.0
     stages = {k: {"avg_ms": (v[0] / v[1]) if v[1] else 0.0, "timed_launches": v[1]}
               for k, v in kt.items() if v[1]}
     res = dict(
         value=value, ms_per_step=ms_step, stages=stages,
         step_ms={"median": float(np.median(per_step)), "p10": float(np.percentile(per_step, 10)),
                  "p90": float(np.percentile(per_step, 90)), "steps": steps},
-        roofline={"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                  "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic.get(kname),
-                  "kernel": f"k_mlp_bf16<{sp.hidden}> ({pipeline})",
-                  "flop_per_launch": flops, "avg_launch_ms": k_avg_ms,
-                  # the predictor and the quality GEMM together, per chunk
-                  "with_quality": {"achieved": with_q, "frac": with_q / PEAK_BF16_TFLOPS,
-                                   "flop_per_chunk": flops + qflops}},
-        # per chunk: embeddings read, Q matrix written, heads read once
-        quality_roofline=hbm_line(nq * (D * 2 + M * 4) + D * 32 * 2, avg("quality"), "k_quality_bf16_lds",
-                                  traffic.get("quality")),
         config={"workload": f"{sp.name} throughput stress: {n} queries x {N} pairs ({M} models x "
                             f"{sp.n_gpu_types} GPU types), embed {D} bf16, predictor "
                             f"{sp.feat_dim}-{sp.hidden}-{sp.hidden}-2 bf16/fp32-acc, "
                             f"{sp.n_chunks} chunks of {nq} on one stream",
-                "queries": n, "pairs": N, "chunk": nq, "pipeline": pipeline, "seed": args.seed},
+                "queries": n, "pairs": N, "chunk": nq, "pipeline": pipeline, "seed": args.seed,
+                "predictor": "once per (query-feature value, pair) of a step" if pipeline == "fused"
+                             else "once per (query, pair)"},
     )
-    if pipeline == "staged":
+    if pipeline == "fused":
+        # decisions with the qualities inside, per chunk: embeddings, lengths,
+        # N_out and bounds read, choice, feasible and four floats written
+        res["roofline"] = hbm_line(nq * (D * 2 + 12 + 21) + D * 32 * 2, avg("fused"), "k_route", traffic.get("fused"))
+        # the predictor runs once per (query-feature value, pair) of a step,
+        # into the table the decisions read; a batch holds this many values
+        feature = np.log(w["il"].cpu().numpy().astype(np.float64)) * 0.125
+        from paper_2608_14575_amd.synth import f32_to_bf16_bits
+        values = int(np.unique(f32_to_bf16_bits(feature.astype(np.float32))).size)
+        res["predictor_table"] = {"avg_launch_ms": avg("mlp"), "launches_per_step": 1, "feature_values_in_batch": values,
+                                  "kernel": f"k_table<{sp.hidden}>"}
+    else:
+        flops = predictor_flops(sp.feat_dim, sp.hidden) * chunk_cands
+        achieved = flops / (avg("mlp") / 1e3) / 1e12
+        res["roofline"] = {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                           "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic.get("mlp"),
+                           "kernel": f"k_mlp_bf16<{sp.hidden}> (staged)", "flop_per_launch": flops,
+                           "avg_launch_ms": avg("mlp")}
+        # per chunk: embeddings read, Q matrix written, heads read once
+        res["quality_roofline"] = hbm_line(nq * (D * 2 + M * 4) + D * 32 * 2, avg("quality"), "k_quality_bf16_lds",
+                                           traffic.get("quality"))
         # gather: writes the feature matrix X (64 B per candidate), reads the
         # input lengths and the pair rows; epilogue: reads TTFT and TPOT
         # (8 B per candidate), the Q matrix, N_out and the bound, writes
@@ -545,8 +551,6 @@ def with_achievable(line: dict, ceilings: dict) -> dict:
         peak = ceilings["hbm_write_gbs" if line.get("hbm_dir") == "write" else "hbm_read_gbs"]
     line["achievable_peak"] = peak
     line["achievable_frac"] = line["achieved"] / peak if peak > 0 else None
-    if "with_quality" in line:
-        line["with_quality"]["achievable_frac"] = line["with_quality"]["achieved"] / peak if peak > 0 else None
     return line
 
 
@@ -616,13 +620,15 @@ def main() -> int:
         return 0
     w = prepare(args, S, torch)
     res = throughput(args, hwr, torch, w, args.pipeline, args.steps, args.warmup)
-    log(f"throughput {res['value']:.3e} candidates/s, predictor {res['roofline']['achieved']:.1f} TFLOP/s")
+    log(f"throughput {res['value']:.3e} candidates/s, {res['roofline']['kernel']} "
+        f"{res['roofline']['achieved']:.1f} {res['roofline']['unit']}")
     staged = None
     if args.pipeline == "fused" and args.staged_steps > 0:
         sr = throughput(args, hwr, torch, w, "staged", args.staged_steps, 1)
         staged = {"value": sr["value"], "unit": "candidates/s", "ms_per_step": sr["ms_per_step"],
                   "steps": args.staged_steps, "gather_roofline": sr["gather_roofline"],
                   "epilogue_roofline": sr["epilogue_roofline"], "mlp_roofline": sr["roofline"],
+                  "quality_roofline": sr["quality_roofline"],
                   "stages": sr["stages"]}
         log(f"staged: gather {sr['gather_roofline']['frac']:.2f} of HBM, "
             f"epilogue {sr['epilogue_roofline']['frac']:.2f} of HBM")
@@ -631,9 +637,10 @@ def main() -> int:
     ceilings = None if args.no_peak_probe else peak_probes(hwr, torch)
     if ceilings:
         with_achievable(res["roofline"], ceilings)
-        with_achievable(res["quality_roofline"], ceilings)
+        if "quality_roofline" in res:
+            with_achievable(res["quality_roofline"], ceilings)
         if staged:
-            for k in ("gather_roofline", "epilogue_roofline", "mlp_roofline"):
+            for k in ("gather_roofline", "epilogue_roofline", "mlp_roofline", "quality_roofline"):
                 with_achievable(staged[k], ceilings)
     single = None if args.no_single else single_query(args, S, hwr, torch)
     single_graph = None if args.no_single else single_query(args, S, hwr, torch, hwr.HWR_FLAG_GRAPH)
@@ -667,7 +674,8 @@ def main() -> int:
         "config": res["config"], "roofline": res["roofline"], "cpu_baseline": cpu,
         "single_query": single, "single_query_graph_launch": single_graph,
         "single_query_resident": single_res, "single_query_launch_floor": floor,
-        "step_ms": res["step_ms"], "quality_roofline": res["quality_roofline"], "stages": res["stages"],
+        "step_ms": res["step_ms"], "quality_roofline": res.get("quality_roofline"),
+        "predictor_table": res.get("predictor_table"), "stages": res["stages"],
         "staged_pipeline": staged, "ceilings": ceilings, "batch_latency": batch, "host_batches": hostb,
         "closed_loop": sim, "closed_loop_pareto": pareto,
     }

@@ -85,11 +85,14 @@ typedef enum {
 typedef enum { HWR_F32 = 0, HWR_BF16 = 1 } hwr_dtype;
 typedef enum { HWR_MEM_DEVICE = 0, HWR_MEM_HOST = 1 } hwr_mem;
 
-/* How a batch is computed.  FUSED: quality kernel, then one kernel that
- * assembles features, runs the predictor and the decision per candidate
- * without writing per-candidate data.  STAGED: quality, feature gather (writes
- * X[q][d][32] bf16), predictor (writes TTFT/TPOT per candidate), decision --
- * each stage a separate kernel.  Both give the same results. */
+/* How a batch is computed.  FUSED: a predictor table, then the decisions from
+ * it, without writing per-candidate data (bf16).  The predictor's only query
+ * input is bf16(ln(input_len) / 8), which takes about 350 values over all
+ * lengths: a call with more queries than that runs the predictor once per
+ * (value, pair), a smaller one once per (query, pair).  STAGED: quality,
+ * feature gather (writes X[d][q][32] bf16), predictor on every candidate
+ * (writes TTFT/TPOT per candidate), decision -- each stage a separate kernel.
+ * Both give the same results. */
 typedef enum { HWR_PIPE_FUSED = 0, HWR_PIPE_STAGED = 1 } hwr_pipeline;
 
 /* hwr_config.flags */
@@ -229,9 +232,8 @@ hwr_status hwr_route_batch(hwr_ctx *ctx, const hwr_query_batch *q, hwr_route_res
  * forbid hipMalloc.  Same arguments, results and ordering as hwr_route_batch
  * for HWR_MEM_DEVICE batches, bit for bit; it calls no hipMalloc, hipFree or
  * other allocating routine (and creates no events: kernel timing is skipped).
- * Its work space -- the quality matrix, the split partials and, for staged,
- * fp32 and several-weight contexts, the per-candidate predictions and
- * features -- lives in a static 64 MiB device array of the library, one per
+ * Its work space -- the quality matrix, the predictor table and, for staged and
+ * fp32 contexts, the per-candidate predictions and features -- lives in a static 64 MiB device array of the library, one per
  * GPU, held until the process ends (its address is taken by the first
  * hwr_init on each device).  A batch is routed in chunks of as many queries
  * as that space holds (at most max_chunk); HWR_ERR_UNSUPPORTED when a single
@@ -254,8 +256,13 @@ const char *hwr_last_error(const hwr_ctx *ctx);
 /* Kernel timing: each kernel launch carries two HIP events that its dispatch
  * records at the kernel's start and end, on the stream it runs on (a graph
  * launch of the single-query path is bracketed by events instead).
- * fp32 chunks small enough for the predictor and the quality rows to share
- * the device run both in the predictor's launch: HWR_K_MLP, no HWR_K_QUALITY.
+ * The fused pipeline's decisions are HWR_K_FUSED.  Its predictor table runs
+ * inside the quality launch (HWR_K_QUALITY) on small chunks; chunks of 64
+ * queries per compute unit or more compute the qualities inside the decision
+ * kernel instead (no HWR_K_QUALITY), and the table is HWR_K_MLP.  fp32 chunks
+ * small enough for the predictor and the quality rows to share the device run
+ * both in the predictor's launch: HWR_K_MLP, no HWR_K_QUALITY.  HWR_K_MERGE is
+ * kept for its index; no kernel reports it.
  * Indices of hwr_kernel_times.ms / launches: */
 enum {
     HWR_K_STATE = 0, HWR_K_QUALITY = 1, HWR_K_GATHER = 2, HWR_K_MLP = 3,

@@ -46,14 +46,11 @@ struct Pending {
 };
 
 // Work space of one batch route: where the chunk loop keeps the quality
-// matrix, the split partials and (staged, fp32 and several-weight routes)
-// the per-candidate predictions and features; and how many queries a chunk
-// may hold.
+// matrix, the predictor table (fused) and the per-candidate predictions and
+// features (staged and fp32); and how many queries a chunk may hold.
 struct Workspace {
     float *qmat = nullptr;
-    uint64_t *pkey = nullptr;
-    float *pval = nullptr;
-    size_t part_cap = 0;
+    float *tab = nullptr, *tab_nout = nullptr;
     float *ctt = nullptr, *ctp = nullptr, *cno = nullptr;
     uint16_t *X = nullptr;
     int max_chunk = 0;
@@ -215,9 +212,10 @@ struct hwr_ctx {
     // work space
     float *d_qmat = nullptr, *d_ctt = nullptr, *d_ctp = nullptr, *d_cno = nullptr;
     uint16_t *d_X = nullptr;
-    uint64_t *d_pkey = nullptr;
-    float *d_pval = nullptr;
-    size_t part_cap = 0;
+    float *d_tab = nullptr, *d_tab_nout = nullptr;   // predictor table [len_rows][table_stride(N)]
+    uint16_t *d_len_row = nullptr;    // [kLenBits] feature value (len_index) -> table row
+    uint16_t *d_row_bits = nullptr;   // [len_rows] the values of the bf16 query feature, ascending (same allocation)
+    int len_rows = 0;
     void *scratch = nullptr;          // this device's static scratch (hwr_route_batch_static)
     // host-memory batches: device staging.  Inputs are double-buffered (the
     // next chunk's upload overlaps this chunk's kernels); outputs are ordered
@@ -580,8 +578,8 @@ void release(hwr_ctx *c) {
                         c->d_pair_params, c->d_dep_f32,
                         c->d_dep_bf16, c->d_bq, c->d_wq_pk, c->d_wqT, c->d_w1_pk, c->d_w2_pk,
                         c->d_b1_pk, c->d_b2_pk, c->d_w3_pk, c->d_w3_frag, c->d_wq, c->d_w1, c->d_w2, c->d_w3,
-                        c->d_b1, c->d_b2, c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno, c->d_X, c->d_pkey,
-                        c->d_pval, c->hin[0].emb, c->hin[0].len, c->hin[0].nout, c->hin[0].slo,
+                        c->d_b1, c->d_b2, c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno, c->d_X, c->d_tab,
+                        c->d_tab_nout, c->d_len_row, c->hin[0].emb, c->hin[0].len, c->hin[0].nout, c->hin[0].slo,
                         c->hin[1].emb, c->hin[1].len, c->hin[1].nout, c->hin[1].slo, c->d_hchoice,
                         c->d_hval, c->d_hcand, c->d_hqual, c->d_hfeas};
     if (c->cstream) (void)hipStreamSynchronize(c->cstream);
@@ -627,6 +625,28 @@ hwr_status init_impl(const hwr_config *cfg, hwr_ctx **out) {
         release(c);                   // a host allocation failed part-way: nothing is left behind
         throw;
     }
+}
+
+// The values the bf16 query feature takes, ascending, one table row each, and
+// the map from a value (len_index) to its row.  Up to kDense every length is
+// evaluated; from there on consecutive lengths differ by less than a bf16 step,
+// so every bit pattern up to the largest length's is taken.  The host's log
+// agrees with the kernels' (len_feature) on every value: no feature of a length
+// up to kDense lies within 1e-6 of a bf16 rounding boundary, and both are exact
+// to 1e-14 (tests/test_gpu_table.py checks the values on the device).
+hipError_t init_len_rows(hwr_ctx *c) {
+    constexpr int kDense = 256;
+    auto bits = [](int32_t len) { return bf16_rne(static_cast<float>(std::log(static_cast<double>(len)) * 0.125)); };
+    std::vector<uint16_t> row_bits, row(kLenBits, 0);
+    for (int32_t len = 1; len <= kDense; ++len)
+        if (row_bits.empty() || bits(len) != row_bits.back()) row_bits.push_back(bits(len));
+    for (int b = row_bits.back() + 1; b <= bits(INT32_MAX); ++b) row_bits.push_back(static_cast<uint16_t>(b));
+    c->len_rows = static_cast<int>(row_bits.size());
+    for (int r = 0; r < c->len_rows; ++r) row[len_index(row_bits[r])] = static_cast<uint16_t>(r);
+    row.insert(row.end(), row_bits.begin(), row_bits.end());   // one upload: the map, then the values
+    const hipError_t e = upload(&c->d_len_row, row.data(), row.size());
+    c->d_row_bits = c->d_len_row + kLenBits;
+    return e;
 }
 
 // Fills a new context; on an error it releases it (bail).
@@ -730,18 +750,18 @@ hwr_status init_ctx(hwr_ctx *c, const hwr_config *cfg, const hipDeviceProp_t &pr
     const size_t chunk = static_cast<size_t>(c->max_chunk);
     const size_t ldq = static_cast<size_t>(pair_stride(c->max_chunk));   // pair-major row stride
     INIT_HIP(dev_alloc(&c->d_qmat, chunk * M));
-    // per-candidate predictions in HBM: staged and fp32 paths, and several
-    // cost weights (the decisions then run after the predictor)
-    if (!c->bf16 || c->pipeline == HWR_PIPE_STAGED || c->nw > 1) {
+    // per-candidate predictions in HBM: staged and fp32 paths
+    if (!c->bf16 || c->pipeline == HWR_PIPE_STAGED) {
         INIT_HIP(dev_alloc(&c->d_ctt, ldq * N));
         INIT_HIP(dev_alloc(&c->d_ctp, ldq * N));
         if (c->NH == 3) INIT_HIP(dev_alloc(&c->d_cno, ldq * N));
     }
     if (c->bf16 && c->pipeline == HWR_PIPE_STAGED) INIT_HIP(dev_alloc(&c->d_X, ldq * N * kFeatPad));
     if (c->bf16 && c->pipeline == HWR_PIPE_FUSED) {
-        c->part_cap = static_cast<size_t>(2 * c->cus) * kQPerBlock;
-        INIT_HIP(dev_alloc(&c->d_pkey, c->part_cap));
-        INIT_HIP(dev_alloc(&c->d_pval, c->part_cap * kPartVals));
+        INIT_HIP(init_len_rows(c));
+        const size_t entries = static_cast<size_t>(c->len_rows) * table_stride(N);
+        INIT_HIP(dev_alloc(&c->d_tab, entries * 2));
+        if (c->NH == 3) INIT_HIP(dev_alloc(&c->d_tab_nout, entries));
     }
     INIT_HIP(hipHostMalloc(reinterpret_cast<void **>(&c->h_ring),
                            sizeof(hwr_hw_state) * N * kStateSlots, hipHostMallocMapped));
@@ -816,15 +836,71 @@ MlpF32Args f32_args(const hwr_ctx *c, const QueryArgs &qa) {
 Workspace ctx_workspace(const hwr_ctx *c) {
     Workspace w;
     w.qmat = c->d_qmat;
-    w.pkey = c->d_pkey;
-    w.pval = c->d_pval;
-    w.part_cap = c->part_cap;
+    w.tab = c->d_tab;
+    w.tab_nout = c->d_tab_nout;
     w.ctt = c->d_ctt;
     w.ctp = c->d_ctp;
     w.cno = c->d_cno;
     w.X = c->d_X;
     w.max_chunk = c->max_chunk;
     return w;
+}
+
+PredictorWeights predictor_weights(const hwr_ctx *c) {
+    return PredictorWeights{c->d_w1_pk, c->d_w2_pk, c->d_b1_pk, c->d_b2_pk, c->d_w3_frag, c->b3[0], c->b3[1], c->b3[2]};
+}
+
+// One chunk of the fused pipeline.  Chunks that give every compute unit a
+// 64-query workgroup compute the qualities inside the decision kernel, which
+// streams the embeddings at the rate of a quality kernel alone and hides the
+// decisions under other workgroups' loads; smaller chunks run the quality tiles
+// beside the predictor table, in the same launch, and the decisions after it.
+hwr_status route_fused(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, const OutArgs &oa, const Workspace &w,
+                       bool by_value, bool need_table, float *ctt, float *ctp, float *cno, bool want_quality) {
+    const int cn = qa.nq;
+    TableArgs ta{};
+    ta.rows = by_value ? c->len_rows : cn;
+    ta.N = c->N;
+    ta.ldn = table_stride(c->N);
+    ta.len_slot = c->len_slot;
+    ta.nheads = c->NH;
+    ta.fold_b1 = c->fold_b1;
+    ta.row_bits = by_value ? c->d_row_bits : nullptr;
+    ta.input_len = qa.input_len;
+    ta.dep_bf16 = c->d_dep_bf16;
+    ta.w = predictor_weights(c);
+    ta.tab = w.tab;
+    ta.tab_nout = w.tab_nout;
+    RouteArgs ra{};
+    ra.N = c->N;
+    ra.M = c->M;
+    ra.ldn = ta.ldn;
+    ra.rule = c->rule;
+    ra.nw = c->nw;
+    for (int k = 0; k < c->nw; ++k) ra.w[k] = c->w[k];
+    ra.q = qa;
+    ra.dep_model = c->d_dep_model;
+    ra.tab = w.tab;
+    ra.tab_nout = c->NH == 3 ? w.tab_nout : nullptr;
+    ra.len_row = by_value ? c->d_len_row : nullptr;
+    ra.quality = qu;
+    ra.dbg_ttft = ctt;
+    ra.dbg_tpot = ctp;
+    ra.dbg_nout = cno;
+    ra.out = oa;
+    const bool quality_inside = (cn + 63) / 64 >= c->cus;
+    if (quality_inside) {
+        if (need_table) HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_table(c->H, ta, c->cus, c->stream); }));
+        if (!want_quality) ra.quality.qmat = nullptr;
+    } else {
+        HWR_HIP(c, timed(c, HWR_K_QUALITY, [&] {
+            if (!need_table) return launch_quality_bf16(qu, c->cus, c->stream);
+            ta.quality = qu;
+            return launch_table(c->H, ta, c->cus, c->stream);
+        }));
+    }
+    HWR_HIP(c, timed(c, HWR_K_FUSED, [&] { return launch_route(ra, quality_inside, c->stream); }));
+    return HWR_OK;
 }
 
 hwr_status route_device(hwr_ctx *c, const DevBatch &b, const Workspace &w) {
@@ -838,6 +914,11 @@ hwr_status route_device(hwr_ctx *c, const DevBatch &b, const Workspace &w) {
     }
     const int M = c->M, N = c->N, D = c->D;
     const size_t esz = c->bf16 ? 2 : 4;
+    const bool fused = c->bf16 && c->pipeline == HWR_PIPE_FUSED;
+    // Fused: the predictor runs once per (feature value, pair), or per (query,
+    // pair) when the batch has no more queries than the feature has values
+    // (fewer evaluations either way); the values' table serves every chunk.
+    const bool by_value = fused && b.n > c->len_rows;
     for (int off = 0; off < b.n; off += w.max_chunk) {
         const int cn = std::min(w.max_chunk, b.n - off);
         const int ldq = pair_stride(cn);       // pair-major row stride of this chunk
@@ -875,6 +956,11 @@ hwr_status route_device(hwr_ctx *c, const DevBatch &b, const Workspace &w) {
         // rows inside the predictor launch, in workgroups of their own.
         const bool quality_inside =
             !c->bf16 && mlp_f32_blocks(static_cast<long>(cn) * N) + (cn + 3) / 4 <= c->cus;
+        if (fused) {
+            st = route_fused(c, qu, qa, oa, w, by_value, !by_value || off == 0, ctt, ctp, cno, b.cand_quality != nullptr);
+            if (st != HWR_OK) return st;
+            continue;
+        }
         if (!quality_inside) {
             HWR_HIP(c, timed(c, HWR_K_QUALITY, [&] {
                 return c->bf16 ? launch_quality_bf16(qu, c->cus, c->stream) : launch_quality_f32(qu, c->stream);
@@ -884,74 +970,22 @@ hwr_status route_device(hwr_ctx *c, const DevBatch &b, const Workspace &w) {
         if (c->bf16) {
             MlpArgs ma{};
             ma.N = N;
-            ma.M = M;
-            ma.len_slot = c->len_slot;
-            ma.rule = c->rule;
-            ma.w = c->w[0];
-            ma.b3_0 = c->b3[0];
-            ma.b3_1 = c->b3[1];
-            ma.b3_2 = c->b3[2];
+            ma.nq = cn;
             ma.nheads = c->NH;
-            ma.q = qa;
-            ma.dep_bf16 = c->d_dep_bf16;
-            ma.dep_model = c->d_dep_model;
-            ma.qmat = qmat;
-            ma.w1_pk = c->d_w1_pk;
-            ma.w2_pk = c->d_w2_pk;
-            ma.b1_pk = c->d_b1_pk;
-            ma.b2_pk = c->d_b2_pk;
             ma.fold_b1 = c->fold_b1;
-            ma.w3_frag = c->d_w3_frag;
-            ma.out = oa;
-            ma.nsplit = 1;
+            ma.w = predictor_weights(c);
             ma.ldq = ldq;
             // one wave per SIMD with four column tiles pays where every
             // compute unit gets a workgroup; smaller batches take the two-tile
             // form (two waves per SIMD), which starts and drains faster
             ma.four_tiles = (cn + kQPerBlock - 1) / kQPerBlock >= c->cus;
-            if (c->pipeline == HWR_PIPE_FUSED && c->nw == 1) {
-                // per-candidate outputs, if the caller asked for them, go
-                // straight to its [query][pair] buffers
-                ma.cand_ttft = ctt;
-                ma.cand_tpot = ctp;
-                ma.cand_nout = cno;
-                ma.cand_pm = 0;
-                const int blocks = (cn + kQPerBlock - 1) / kQPerBlock;
-                int nsplit = 1;
-                if (blocks < c->cus) nsplit = std::min(N, (c->cus + blocks - 1) / blocks);
-                while (nsplit > 1 && static_cast<size_t>(nsplit) * cn > w.part_cap) --nsplit;
-                ma.nsplit = nsplit;
-                ma.part_key = w.pkey;
-                ma.part_val = w.pval;
-                HWR_HIP(c, timed(c, HWR_K_FUSED, [&] { return launch_mlp_bf16(c->H, false, ma, c->stream); }));
-                if (nsplit > 1) {
-                    MergeArgs mg{cn, nsplit, w.pkey, w.pval, oa};
-                    HWR_HIP(c, timed(c, HWR_K_MERGE, [&] { return launch_merge(mg, c->stream); }));
-                }
-                continue;
-            }
-            if (c->pipeline == HWR_PIPE_FUSED) {
-                // several cost weights: the fused kernel writes every
-                // candidate's predictions (pair-major, into the work space)
-                // and no decision; the epilogue below takes one decision per
-                // weight
-                ma.cand_ttft = w.ctt;
-                ma.cand_tpot = w.ctp;
-                ma.cand_nout = c->NH == 3 ? w.cno : nullptr;
-                ma.cand_pm = 1;
-                ma.out = OutArgs{};
-                ma.nsplit = 1;
-                HWR_HIP(c, timed(c, HWR_K_FUSED, [&] { return launch_mlp_bf16(c->H, false, ma, c->stream); }));
-            } else {
-                GatherArgs ga{N, c->len_slot, qa, c->d_dep_bf16, w.X, ldq};
-                HWR_HIP(c, timed(c, HWR_K_GATHER, [&] { return launch_gather(ga, c->stream); }));
-                ma.X = w.X;
-                ma.cand_ttft = w.ctt;
-                ma.cand_tpot = w.ctp;
-                ma.cand_nout = w.cno;
-                ma.cand_pm = 1;
-                HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_bf16(c->H, true, ma, c->stream); }));
-            }
+            GatherArgs ga{N, c->len_slot, qa, c->d_dep_bf16, w.X, ldq};
+            HWR_HIP(c, timed(c, HWR_K_GATHER, [&] { return launch_gather(ga, c->stream); }));
+            ma.X = w.X;
+            ma.cand_ttft = w.ctt;
+            ma.cand_tpot = w.ctp;
+            ma.cand_nout = w.cno;
+            HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_bf16(c->H, ma, c->stream); }));
         } else {
             MlpF32Args fa = f32_args(c, qa);
             fa.ldq = ldq;
@@ -1358,22 +1392,21 @@ hwr_status check_route_args(hwr_ctx *c, const hwr_query_batch *q, const hwr_rout
     return HWR_OK;
 }
 
-// Work space carved out of this device's static scratch: the split partials
-// (fused, one weight) first, then per chunk row the quality row, the
-// per-candidate predictions (staged, fp32 and several-weight routes) and the
-// staged features, each block 256-byte aligned.  Chunks hold as many queries
-// as fit, at most max_chunk; 0 rows: one query does not fit.
+// Work space carved out of this device's static scratch: the predictor table
+// (fused) first, then per chunk row the quality row, the per-candidate
+// predictions (staged and fp32 routes) and the staged features, each block
+// 256-byte aligned.  Chunks hold as many queries as fit, at most max_chunk;
+// 0 rows: one query does not fit.
 Workspace scratch_workspace(const hwr_ctx *c) {
     Workspace w;
     w.timing = false;
     const size_t M = c->M, N = c->N;
-    const bool fused1 = c->bf16 && c->pipeline == HWR_PIPE_FUSED && c->nw == 1;
-    const bool per_cand = !c->bf16 || c->pipeline == HWR_PIPE_STAGED || c->nw > 1;
+    const bool fused = c->bf16 && c->pipeline == HWR_PIPE_FUSED;
     const bool staged = c->bf16 && c->pipeline == HWR_PIPE_STAGED;
     auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
-    const size_t part_cap = fused1 ? static_cast<size_t>(2 * c->cus) * kQPerBlock : 0;
-    const size_t fixed = up(part_cap * sizeof(uint64_t)) + up(part_cap * kPartVals * sizeof(float));
-    const size_t row = M * 4 + (per_cand ? N * 4 * (c->NH == 3 ? 3 : 2) : 0) + (staged ? N * kFeatPad * 2 : 0);
+    const size_t entries = fused ? static_cast<size_t>(c->len_rows) * table_stride(c->N) : 0;
+    const size_t fixed = up(entries * 8) + (c->NH == 3 ? up(entries * 4) : 0);
+    const size_t row = M * 4 + (fused ? 0 : N * 4 * (c->NH == 3 ? 3 : 2)) + (staged ? N * kFeatPad * 2 : 0);
     // alignment of the per-row blocks, and the pair-major rows padded to
     // pair_stride(rows) (at most kPairAlign - 1 more rows)
     const size_t slack = 5 * 256 + (kPairAlign - 1) * row;
@@ -1388,13 +1421,12 @@ Workspace scratch_workspace(const hwr_ctx *c) {
         off += up(bytes);
         return p;
     };
-    if (fused1) {
-        w.pkey = reinterpret_cast<uint64_t *>(take(part_cap * sizeof(uint64_t)));
-        w.pval = reinterpret_cast<float *>(take(part_cap * kPartVals * sizeof(float)));
-        w.part_cap = part_cap;
+    if (fused) {
+        w.tab = reinterpret_cast<float *>(take(entries * 8));
+        if (c->NH == 3) w.tab_nout = reinterpret_cast<float *>(take(entries * 4));
     }
     w.qmat = reinterpret_cast<float *>(take(rows * M * 4));
-    if (per_cand) {
+    if (!fused) {
         w.ctt = reinterpret_cast<float *>(take(ldq * N * 4));
         w.ctp = reinterpret_cast<float *>(take(ldq * N * 4));
         if (c->NH == 3) w.cno = reinterpret_cast<float *>(take(ldq * N * 4));

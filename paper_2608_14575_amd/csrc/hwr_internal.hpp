@@ -15,14 +15,13 @@ namespace hwr {
 constexpr int kFeatPad = 32;     // feature slots padded to two 16-wide MFMA k-blocks
 constexpr int kQualTile = 32;    // quality GEMM: models padded to one 32-wide tile
 constexpr int kBlock = 256;      // threads per workgroup of the batch kernels
-constexpr int kQPerWave = 64;    // fused predictor: queries per wave (two 32-column tiles)
+constexpr int kQPerWave = 64;    // staged predictor: queries per wave in the two-tile form
 constexpr int kQPerBlock = kQPerWave * 4;   // four query sub-blocks per workgroup
 constexpr int kMlpThreads = 512;             // predictor workgroup with two column tiles per wave: 8 waves
 constexpr int kGatherQ = 256;    // feature gather: queries per workgroup (one wave per SIMD)
 constexpr int kMaxPairs = 1024;
 constexpr int kMaxModels = 32;
 constexpr int kMaxHeads = 3;     // predictor outputs: TTFT, TPOT and (optionally) N_out
-constexpr int kPartVals = 8;     // floats per split partial: u, C, TTFT, TPOT, N_out, pad
 constexpr int kMaxWeights = 8;   // cost weights scored in one call (HWR_MAX_WEIGHTS)
 // Layer-1 bias folded into the first MFMA layer (bf16 predictor): feature
 // slots kFoldSlot .. kFoldSlot + 2 of the bf16 pair rows hold 1.0 and the
@@ -89,6 +88,19 @@ __device__ inline uint64_t decision_key(bool feasible, float u, int d) {
 __device__ inline int key_pair(uint64_t k) { return 0x7FFFFFFF - static_cast<int>(k & 0x7FFFFFFFull); }
 __device__ inline bool key_feasible(uint64_t k) { return (k >> 63) != 0; }
 
+// The query feature of the bf16 predictor, bf16(ln(input_len) / 8), takes few
+// values: 0 for input_len 1, then bit patterns from that of input_len 2
+// (0x3DB1) to that of 2^31 - 1 (0x402C).  len_index maps them onto
+// 0 .. kLenBits - 1.
+constexpr int kLenBits0 = 0x3DB0, kLenBits = 0x402C - kLenBits0 + 1;
+__host__ __device__ constexpr int len_index(int bits) {
+    const int i = bits - kLenBits0;
+    return i < 0 ? 0 : i < kLenBits ? i : kLenBits - 1;
+}
+// Pairs per row of the predictor table: even, so that every row starts
+// 16-byte aligned ([row][pair] holds TTFT and TPOT).
+__host__ __device__ constexpr int table_stride(int N) { return (N + 1) & ~1; }
+
 // ---------------------------------------------------------------- arguments
 // Decision rule of a launch (Sec. 3.1 score, Eq. 3 bound).
 struct Rule {
@@ -132,31 +144,56 @@ struct QualityArgs {
     float *qmat;                  // [nq][M]
 };
 
-struct MlpArgs {                  // bf16 predictor (fused or staged)
-    int N, M, len_slot;
-    int nheads;                   // 2, or 3: N_out predicted by the third head
-    Rule rule;
-    float w;                      // cost weight
-    float b3_0, b3_1, b3_2;
-    QueryArgs q;
-    const uint16_t *dep_bf16;     // [N][32]
-    const int32_t *dep_model;     // [N]
-    const float *qmat;            // [nq][M]
+// Packed predictor weights on the device (pack_predictor), bf16 paths.
+struct PredictorWeights {
     const uint16_t *w1_pk, *w2_pk;
     const float *b1_pk, *b2_pk;
-    const uint16_t *w3_frag;      // head layer A fragments (compact, see pack_predictor)
-    const uint16_t *X;            // staged input [N][ldq][32] (pair-major)
-    float *cand_ttft, *cand_tpot; // per-candidate TTFT / TPOT: staged, several weights or debug
-    float *cand_nout;             // predicted N_out (three heads), same layout
-    int cand_pm;                  // 1: pair-major [N][ldq] (staged always); 0: [nq][N]
-    int ldq;                      // pair stride of the pair-major buffers: pair_stride(nq)
-    OutArgs out;
-    int nsplit;                   // pair ranges (grid.y); >1 writes partials
+    const uint16_t *w3_frag;      // head layer A fragments (compact)
+    float b3_0, b3_1, b3_2;
+};
+
+struct MlpArgs {                  // staged bf16 predictor
+    int N, nq;
+    int nheads;                   // 2, or 3: N_out predicted by the third head
+    int fold_b1;                  // b1 is inside W1 (zero accumulator start)
     int four_tiles;               // the batch fills the device (a workgroup per compute unit or more):
                                   // the four-tile form, where it exists for H
-    uint64_t *part_key;           // [nsplit][nq]
-    float *part_val;              // [nsplit][nq][kPartVals]
-    int fold_b1;                  // b1 is inside W1 (zero accumulator start)
+    PredictorWeights w;
+    const uint16_t *X;            // [N][ldq][32], pair-major
+    float *cand_ttft, *cand_tpot, *cand_nout;   // [N][ldq]; cand_nout: three heads only
+    int ldq;                      // pair stride of the pair-major buffers: pair_stride(nq)
+};
+
+// Predictor table of the fused pipeline: TTFT and TPOT (and N_out) of every
+// (row, pair), a row being one value of the query feature.
+struct TableArgs {
+    int rows, N, ldn;             // ldn: pairs per table row (table_stride(N))
+    int len_slot, nheads, fold_b1;
+    const uint16_t *row_bits;     // [rows] the rows' features (bf16 bits), or null:
+    const int32_t *input_len;     // row r is the feature of input_len[r]
+    const uint16_t *dep_bf16;     // [N][32]
+    PredictorWeights w;
+    float *tab;                   // [rows][ldn][2]: TTFT, TPOT
+    float *tab_nout;              // [rows][ldn] (three heads)
+    int blocks;                   // workgroups of the table (set by the launcher)
+    int qual_waves;               // quality tiles per workgroup past them (0: none)
+    QualityArgs quality;
+};
+
+// Decisions of the fused pipeline: quality (read, or computed from the
+// embeddings), then Eq. 2 and Eq. 3 over every pair of the query's table row.
+struct RouteArgs {
+    int N, M, ldn;
+    Rule rule;
+    int nw;                       // cost weights (>= 1); outputs are [nq][nw] when nw > 1
+    float w[kMaxWeights];
+    QueryArgs q;
+    const int32_t *dep_model;
+    const float *tab, *tab_nout;  // as in TableArgs; tab_nout null: the query's given N_out
+    const uint16_t *len_row;      // [kLenBits] table row by feature bits (len_index), or null: row = query
+    QualityArgs quality;
+    float *dbg_ttft, *dbg_tpot, *dbg_nout;   // caller's per-candidate outputs [nq][N], or null
+    OutArgs out;
 };
 
 struct MlpF32Args {
@@ -193,13 +230,6 @@ struct EpilogueArgs {
     const float *cand_ttft, *cand_tpot;   // [N][ldq], 16-byte aligned
     const float *cand_nout;       // [N][ldq] predicted N_out, or null: the query's given N_out
     float *dbg_ttft, *dbg_tpot, *dbg_nout;   // caller's per-candidate outputs [nq][N], or null
-    OutArgs out;
-};
-
-struct MergeArgs {
-    int nq, nsplit;
-    const uint64_t *part_key;
-    const float *part_val;
     OutArgs out;
 };
 
@@ -246,12 +276,16 @@ hipError_t launch_state(const StateArgs &a, hipStream_t s);
 // cus: compute units of the device (a grid below it takes the unrolled variant)
 hipError_t launch_quality_bf16(const QualityArgs &a, int cus, hipStream_t s);
 hipError_t launch_quality_f32(const QualityArgs &a, hipStream_t s);
-hipError_t launch_mlp_bf16(int H, bool staged, const MlpArgs &a, hipStream_t s);
+hipError_t launch_mlp_bf16(int H, const MlpArgs &a, hipStream_t s);   // staged
+// Table of a.rows x a.N predictions; with a.quality.nq > 0 the same launch runs
+// the quality tiles beside it, in workgroups of their own.
+hipError_t launch_table(int H, const TableArgs &a, int cus, hipStream_t s);
+// Decisions; with_quality: the quality GEMM inside, else from a.quality.qmat.
+hipError_t launch_route(const RouteArgs &a, bool with_quality, hipStream_t s);
 int mlp_f32_blocks(long candidates);   // workgroups of launch_mlp_f32's predictor
 hipError_t launch_mlp_f32(int H, const MlpF32Args &a, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
 hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s);
-hipError_t launch_merge(const MergeArgs &a, hipStream_t s);
 hipError_t launch_single(int H, bool resident, const SingleArgs &a, hipStream_t s);
 
 }  // namespace hwr

@@ -434,29 +434,6 @@ hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s) {
     return table[idx](a, dim3(grid), lds, s);
 }
 
-// ------------------------------------------------------------ split merge
-// When the pairs of a chunk are split over several workgroups, each writes
-// its best key and values; this picks the maximum key per query.
-__global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= a.nq) return;
-    uint64_t best = 0;
-    int bs = 0;
-    for (int s = 0; s < a.nsplit; ++s) {
-        const uint64_t k = a.part_key[static_cast<size_t>(s) * a.nq + q];
-        if (k > best) {
-            best = k;
-            bs = s;
-        }
-    }
-    const float *v = a.part_val + (static_cast<size_t>(bs) * a.nq + q) * kPartVals;
-    write_outputs(a.out, q, best, v[0], v[1], v[2], v[3], v[4]);
-}
-
-hipError_t launch_merge(const MergeArgs &a, hipStream_t s) {
-    return launch_kernel(k_merge, dim3((a.nq + 255) / 256), dim3(256), 0, s, a);
-}
-
 }  // namespace hwr
 
 // ------------------------------------------------------------ feature log check
