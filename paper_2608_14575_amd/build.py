@@ -16,7 +16,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libhwr.so")
 BUILD = os.path.join(PKG, "_build")
 
-SOURCES = ["hwr_api.hip", "k_common.hip", "k_bf16.hip", "k_table.hip", "k_route.hip", "k_single.hip", "k_probe.hip", "hwr_sim.cpp"]
+SOURCES = ["hwr_api.hip", "k_common.hip", "k_bf16.hip", "k_table.hip", "k_route.hip", "k_f32.hip",
+           "k_single.hip", "k_probe.hip", "hwr_sim.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -32,9 +33,9 @@ FLAGS = [
 
 # Per-source flags.  MFMA results in vector registers (VGPR form): k_bf16.hip,
 # so that the accumulation registers stay free for the four-tile predictor's
-# first-layer activations, which its MFMAs read directly; k_table.hip and
-# k_route.hip, whose vector code reads the results.
-EXTRA = {k: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for k in ("k_bf16.hip", "k_table.hip", "k_route.hip")}
+# first-layer activations, which its MFMAs read directly; k_table.hip,
+# k_route.hip and k_f32.hip, whose vector code reads the results.
+EXTRA = {k: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for k in ("k_bf16.hip", "k_table.hip", "k_route.hip", "k_f32.hip")}
 
 
 def _compile(src: str) -> str:

@@ -46,11 +46,12 @@ struct Pending {
 };
 
 // Work space of one batch route: where the chunk loop keeps the quality
-// matrix, the predictor table (fused) and the per-candidate predictions and
-// features (staged and fp32); and how many queries a chunk may hold.
+// matrix, the predictor table (fused and fp32) and the per-candidate predictions
+// and features (staged); and how many queries a chunk may hold.
 struct Workspace {
     float *qmat = nullptr;
     float *tab = nullptr, *tab_nout = nullptr;
+    int32_t *owner = nullptr;       // fp32
     float *ctt = nullptr, *ctp = nullptr, *cno = nullptr;
     uint16_t *X = nullptr;
     int max_chunk = 0;
@@ -180,6 +181,7 @@ struct hwr_ctx {
     int M = 0, G = 0, N = 0, A = 0, Gw = 0, D = 0, F = 0, H = 0, len_slot = 0;
     int bf16 = 0, pipeline = 0, max_chunk = 0, flags = 0, cus = 0;
     int NH = 2;                   // predictor heads (3: N_out predicted)
+    int kq = 2;                   // fp32: layer-1 k-steps / 4
     int fold_b1 = 0;              // b1 carried by the first layer's MFMA (bf16)
     float default_slo = 1.0f, b3[kMaxHeads] = {0, 0, 0};
     Rule rule{};                  // score and bound modes
@@ -207,8 +209,8 @@ struct hwr_ctx {
     float *d_b1_pk = nullptr, *d_b2_pk = nullptr;
     uint32_t *d_w3_pk = nullptr;
     uint16_t *d_w3_frag = nullptr;
-    float *d_wq = nullptr, *d_w1 = nullptr, *d_w2 = nullptr, *d_w3 = nullptr, *d_b1 = nullptr,
-          *d_b2 = nullptr;
+    float *d_wq = nullptr, *d_f32 = nullptr;   // fp32: packed quality heads and predictor
+    int32_t *d_owner = nullptr;       // fp32: [kOwnLens] a chunk's owner of each length
     // work space
     float *d_qmat = nullptr, *d_ctt = nullptr, *d_ctp = nullptr, *d_cno = nullptr;
     uint16_t *d_X = nullptr;
@@ -330,6 +332,54 @@ struct PackedPredictor {
     std::vector<float> b1, b2;
     std::vector<uint32_t> w3;
 };
+
+// fp32 quality B operands: for 64-wide slice s, k-steps 4 j .. 4 j + 3, model
+// tile t and lane (n, g), element i holds Wq[64 s + 16 g + 4 j + i][16 t + n]
+// (zero for padded models).
+std::vector<float> pack_quality_f32(const float *wq, int D, int M) {
+    std::vector<float> out(static_cast<size_t>(D) * 32, 0.0f);
+    for (int s = 0; s < D / 64; ++s)
+        for (int j = 0; j < 4; ++j)
+            for (int t = 0; t < 2; ++t)
+                for (int lane = 0; lane < 64; ++lane)
+                    for (int i = 0; i < 4; ++i) {
+                        const int m = 16 * t + (lane & 15), k = 64 * s + 16 * (lane >> 4) + 4 * j + i;
+                        if (m < M)
+                            out[((((static_cast<size_t>(s) * 4 + j) * 2 + t) * 64) + lane) * 4 + i] =
+                                wq[static_cast<size_t>(k) * M + m];
+                    }
+    return out;
+}
+
+// fp32 predictor, laid out as F32Weights<H>.  Layer 1 A operands: lane (n, g),
+// k-step s holds W1[4 kq g + s][16 rt + n] (zero past F).  Layer 2: lane (n, g)
+// of k tile t, k-step i holds W2[16 t + 4 g + i][16 rt + n].  Heads
+// [tile][head][group][4] and biases [tile][group][4] in unit order.
+std::vector<float> pack_predictor_f32(const hwr_config *cfg, int kq, int NH) {
+    const int F = cfg->feat_dim, H = cfg->hidden, RT = H / 16;
+    const float *w1 = static_cast<const float *>(cfg->w1), *w2 = static_cast<const float *>(cfg->w2),
+                *w3 = static_cast<const float *>(cfg->w3);
+    std::vector<float> p;
+    p.reserve(static_cast<size_t>(RT) * (2 + RT) * 256 + RT * (kMaxHeads * 16 + 32));
+    for (int rt = 0; rt < RT; ++rt)
+        for (int s = 0; s < 8; s += 4)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int i = 0; i < 4; ++i) {
+                    const int f = 4 * kq * (lane >> 4) + s + i;
+                    p.push_back(s < 4 * kq && f < F ? w1[static_cast<size_t>(f) * H + 16 * rt + (lane & 15)] : 0.0f);
+                }
+    for (int rt = 0; rt < RT; ++rt)
+        for (int t = 0; t < RT; ++t)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int i = 0; i < 4; ++i)
+                    p.push_back(w2[static_cast<size_t>(16 * t + 4 * (lane >> 4) + i) * H + 16 * rt + (lane & 15)]);
+    for (int rt = 0; rt < RT; ++rt)
+        for (int m = 0; m < kMaxHeads; ++m)
+            for (int u = 0; u < 16; ++u) p.push_back(m < NH ? w3[static_cast<size_t>(16 * rt + u) * NH + m] : 0.0f);
+    p.insert(p.end(), cfg->b1, cfg->b1 + H);
+    p.insert(p.end(), cfg->b2, cfg->b2 + H);
+    return p;
+}
 
 // bf16 nearest-even bits of a finite fp32 value, and back.
 uint16_t bf16_rne(float x) {
@@ -577,8 +627,8 @@ void release(hwr_ctx *c) {
     void *dev_ptrs[] = {c->d_dep_model, c->d_dep_gpu, c->d_model_arch, c->d_params, c->d_pair_arch,
                         c->d_pair_params, c->d_dep_f32,
                         c->d_dep_bf16, c->d_bq, c->d_wq_pk, c->d_wqT, c->d_w1_pk, c->d_w2_pk,
-                        c->d_b1_pk, c->d_b2_pk, c->d_w3_pk, c->d_w3_frag, c->d_wq, c->d_w1, c->d_w2, c->d_w3,
-                        c->d_b1, c->d_b2, c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno, c->d_X, c->d_tab,
+                        c->d_b1_pk, c->d_b2_pk, c->d_w3_pk, c->d_w3_frag, c->d_wq, c->d_f32, c->d_owner,
+                        c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno, c->d_X, c->d_tab,
                         c->d_tab_nout, c->d_len_row, c->hin[0].emb, c->hin[0].len, c->hin[0].nout, c->hin[0].slo,
                         c->hin[1].emb, c->hin[1].len, c->hin[1].nout, c->hin[1].slo, c->d_hchoice,
                         c->d_hval, c->d_hcand, c->d_hqual, c->d_hfeas};
@@ -740,26 +790,27 @@ hwr_status init_ctx(hwr_ctx *c, const hwr_config *cfg, const hipDeviceProp_t &pr
         INIT_HIP(upload(&c->d_w3_pk, p.w3.data(), p.w3.size()));
         INIT_HIP(upload(&c->d_w3_frag, p.w3frag.data(), p.w3frag.size()));
     } else {
-        INIT_HIP(upload(&c->d_wq, static_cast<const float *>(cfg->wq), static_cast<size_t>(D) * M));
-        INIT_HIP(upload(&c->d_w1, static_cast<const float *>(cfg->w1), static_cast<size_t>(F) * H));
-        INIT_HIP(upload(&c->d_w2, static_cast<const float *>(cfg->w2), static_cast<size_t>(H) * H));
-        INIT_HIP(upload(&c->d_w3, static_cast<const float *>(cfg->w3), static_cast<size_t>(H) * c->NH));
-        INIT_HIP(upload(&c->d_b1, cfg->b1, H));
-        INIT_HIP(upload(&c->d_b2, cfg->b2, H));
+        const std::vector<float> wq = pack_quality_f32(static_cast<const float *>(cfg->wq), D, M);
+        INIT_HIP(upload(&c->d_wq, wq.data(), wq.size()));
+        c->kq = c->A + c->Gw + 8 <= 16 ? 1 : 2;
+        const std::vector<float> p = pack_predictor_f32(cfg, c->kq, c->NH);
+        INIT_HIP(upload(&c->d_f32, p.data(), p.size()));
+        INIT_HIP(dev_alloc(&c->d_owner, kOwnLens));
     }
     const size_t chunk = static_cast<size_t>(c->max_chunk);
     const size_t ldq = static_cast<size_t>(pair_stride(c->max_chunk));   // pair-major row stride
     INIT_HIP(dev_alloc(&c->d_qmat, chunk * M));
-    // per-candidate predictions in HBM: staged and fp32 paths
-    if (!c->bf16 || c->pipeline == HWR_PIPE_STAGED) {
+    // per-candidate predictions in HBM: staged path
+    if (c->bf16 && c->pipeline == HWR_PIPE_STAGED) {
         INIT_HIP(dev_alloc(&c->d_ctt, ldq * N));
         INIT_HIP(dev_alloc(&c->d_ctp, ldq * N));
         if (c->NH == 3) INIT_HIP(dev_alloc(&c->d_cno, ldq * N));
     }
     if (c->bf16 && c->pipeline == HWR_PIPE_STAGED) INIT_HIP(dev_alloc(&c->d_X, ldq * N * kFeatPad));
-    if (c->bf16 && c->pipeline == HWR_PIPE_FUSED) {
-        INIT_HIP(init_len_rows(c));
-        const size_t entries = static_cast<size_t>(c->len_rows) * table_stride(N);
+    // predictor table: rows by feature value (fused), by query (fp32)
+    if (!c->bf16 || c->pipeline == HWR_PIPE_FUSED) {
+        if (c->bf16) INIT_HIP(init_len_rows(c));
+        const size_t entries = (c->bf16 ? static_cast<size_t>(c->len_rows) : chunk) * table_stride(N);
         INIT_HIP(dev_alloc(&c->d_tab, entries * 2));
         if (c->NH == 3) INIT_HIP(dev_alloc(&c->d_tab_nout, entries));
     }
@@ -813,31 +864,13 @@ hwr_status sync_state(hwr_ctx *c) {
     return HWR_OK;
 }
 
-MlpF32Args f32_args(const hwr_ctx *c, const QueryArgs &qa) {
-    MlpF32Args fa{};
-    fa.N = c->N;
-    fa.F = c->F;
-    fa.len_slot = c->len_slot;
-    fa.b3_0 = c->b3[0];
-    fa.b3_1 = c->b3[1];
-    fa.b3_2 = c->b3[2];
-    fa.nheads = c->NH;
-    fa.q = qa;
-    fa.dep_f32 = c->d_dep_f32;
-    fa.w1 = c->d_w1;
-    fa.b1 = c->d_b1;
-    fa.w2 = c->d_w2;
-    fa.b2 = c->d_b2;
-    fa.w3 = c->d_w3;
-    return fa;
-}
-
 // The context's own work space, allocated by hwr_init for max_chunk queries.
 Workspace ctx_workspace(const hwr_ctx *c) {
     Workspace w;
     w.qmat = c->d_qmat;
     w.tab = c->d_tab;
     w.tab_nout = c->d_tab_nout;
+    w.owner = c->d_owner;
     w.ctt = c->d_ctt;
     w.ctp = c->d_ctp;
     w.cno = c->d_cno;
@@ -848,6 +881,62 @@ Workspace ctx_workspace(const hwr_ctx *c) {
 
 PredictorWeights predictor_weights(const hwr_ctx *c) {
     return PredictorWeights{c->d_w1_pk, c->d_w2_pk, c->d_b1_pk, c->d_b2_pk, c->d_w3_frag, c->b3[0], c->b3[1], c->b3[2]};
+}
+
+// Decisions of a chunk from the predictor table in w (rows by query, unless the
+// caller sets a row map).
+RouteArgs route_args(const hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, const OutArgs &oa, const Workspace &w,
+                     float *ctt, float *ctp, float *cno) {
+    RouteArgs ra{};
+    ra.N = c->N;
+    ra.M = c->M;
+    ra.ldn = table_stride(c->N);
+    ra.rule = c->rule;
+    ra.nw = c->nw;
+    for (int k = 0; k < c->nw; ++k) ra.w[k] = c->w[k];
+    ra.q = qa;
+    ra.dep_model = c->d_dep_model;
+    ra.tab = w.tab;
+    ra.tab_nout = c->NH == 3 ? w.tab_nout : nullptr;
+    ra.quality = qu;
+    ra.dbg_ttft = ctt;
+    ra.dbg_tpot = ctp;
+    ra.dbg_nout = cno;
+    ra.out = oa;
+    return ra;
+}
+
+// One fp32 chunk.  The predictor reads no quality, so a chunk small enough for
+// both to share the device runs the quality in workgroups of the predictor's
+// launch, and the predictor on every candidate: two launches instead of three
+// (64 x 8, H = 64: 7.5 us a call).  Larger chunks let the quality launch pick an owner
+// of each input length, and the predictor computes the owners' rows only.
+hwr_status route_f32(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, const OutArgs &oa, const Workspace &w,
+                     float *ctt, float *ctp, float *cno) {
+    MlpF32Args fa{};
+    fa.N = c->N;
+    fa.ldn = table_stride(c->N);
+    fa.len_slot = c->len_slot;
+    fa.nheads = c->NH;
+    fa.kq = c->kq;
+    fa.q = qa;
+    fa.dep_f32 = c->d_dep_f32;
+    fa.p = F32Predictor{c->d_f32, c->b3[0], c->b3[1], c->b3[2]};
+    fa.owner = w.owner;
+    fa.tab = w.tab;
+    fa.tab_nout = w.tab_nout;
+    fa.quality = qu;
+    RouteArgs ra = route_args(c, qu, qa, oa, w, ctt, ctp, cno);
+    if (static_cast<long>(qa.nq) * c->N <= 16L * c->cus &&
+        mlp_f32_small_blocks(qa.nq, c->N) + quality_f32_blocks(qa.nq) <= c->cus) {
+        HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_f32_small(c->H, fa, c->stream); }));
+    } else {
+        HWR_HIP(c, timed(c, HWR_K_QUALITY, [&] { return launch_quality_f32(qu, qa.input_len, w.owner, c->stream); }));
+        HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_f32(c->H, fa, c->cus, c->stream); }));
+        ra.owner = w.owner;
+    }
+    HWR_HIP(c, timed(c, HWR_K_EPILOGUE, [&] { return launch_route(ra, false, c->stream); }));
+    return HWR_OK;
 }
 
 // One chunk of the fused pipeline.  Chunks that give every compute unit a
@@ -871,23 +960,8 @@ hwr_status route_fused(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, c
     ta.w = predictor_weights(c);
     ta.tab = w.tab;
     ta.tab_nout = w.tab_nout;
-    RouteArgs ra{};
-    ra.N = c->N;
-    ra.M = c->M;
-    ra.ldn = ta.ldn;
-    ra.rule = c->rule;
-    ra.nw = c->nw;
-    for (int k = 0; k < c->nw; ++k) ra.w[k] = c->w[k];
-    ra.q = qa;
-    ra.dep_model = c->d_dep_model;
-    ra.tab = w.tab;
-    ra.tab_nout = c->NH == 3 ? w.tab_nout : nullptr;
+    RouteArgs ra = route_args(c, qu, qa, oa, w, ctt, ctp, cno);
     ra.len_row = by_value ? c->d_len_row : nullptr;
-    ra.quality = qu;
-    ra.dbg_ttft = ctt;
-    ra.dbg_tpot = ctp;
-    ra.dbg_nout = cno;
-    ra.out = oa;
     const bool quality_inside = (cn + 63) / 64 >= c->cus;
     if (quality_inside) {
         if (need_table) HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_table(c->H, ta, c->cus, c->stream); }));
@@ -951,53 +1025,35 @@ hwr_status route_device(hwr_ctx *c, const DevBatch &b, const Workspace &w) {
         qu.wq = c->d_wq;
         qu.bq = c->d_bq;
         qu.qmat = qmat;
-        // fp32: the predictor reads no quality (the epilogue decides), so a
-        // chunk small enough for both to share the device runs the quality
-        // rows inside the predictor launch, in workgroups of their own.
-        const bool quality_inside =
-            !c->bf16 && mlp_f32_blocks(static_cast<long>(cn) * N) + (cn + 3) / 4 <= c->cus;
         if (fused) {
             st = route_fused(c, qu, qa, oa, w, by_value, !by_value || off == 0, ctt, ctp, cno, b.cand_quality != nullptr);
             if (st != HWR_OK) return st;
             continue;
         }
-        if (!quality_inside) {
-            HWR_HIP(c, timed(c, HWR_K_QUALITY, [&] {
-                return c->bf16 ? launch_quality_bf16(qu, c->cus, c->stream) : launch_quality_f32(qu, c->stream);
-            }));
+        if (!c->bf16) {
+            st = route_f32(c, qu, qa, oa, w, ctt, ctp, cno);
+            if (st != HWR_OK) return st;
+            continue;
         }
-
-        if (c->bf16) {
-            MlpArgs ma{};
-            ma.N = N;
-            ma.nq = cn;
-            ma.nheads = c->NH;
-            ma.fold_b1 = c->fold_b1;
-            ma.w = predictor_weights(c);
-            ma.ldq = ldq;
-            // one wave per SIMD with four column tiles pays where every
-            // compute unit gets a workgroup; smaller batches take the two-tile
-            // form (two waves per SIMD), which starts and drains faster
-            ma.four_tiles = (cn + kQPerBlock - 1) / kQPerBlock >= c->cus;
-            GatherArgs ga{N, c->len_slot, qa, c->d_dep_bf16, w.X, ldq};
-            HWR_HIP(c, timed(c, HWR_K_GATHER, [&] { return launch_gather(ga, c->stream); }));
-            ma.X = w.X;
-            ma.cand_ttft = w.ctt;
-            ma.cand_tpot = w.ctp;
-            ma.cand_nout = w.cno;
-            HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_bf16(c->H, ma, c->stream); }));
-        } else {
-            MlpF32Args fa = f32_args(c, qa);
-            fa.ldq = ldq;
-            fa.cand_ttft = w.ctt;
-            fa.cand_tpot = w.ctp;
-            fa.cand_nout = w.cno;
-            if (quality_inside) {
-                fa.with_quality = 1;
-                fa.quality = qu;
-            }
-            HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_f32(c->H, fa, c->stream); }));
-        }
+        HWR_HIP(c, timed(c, HWR_K_QUALITY, [&] { return launch_quality_bf16(qu, c->cus, c->stream); }));
+        MlpArgs ma{};
+        ma.N = N;
+        ma.nq = cn;
+        ma.nheads = c->NH;
+        ma.fold_b1 = c->fold_b1;
+        ma.w = predictor_weights(c);
+        ma.ldq = ldq;
+        // one wave per SIMD with four column tiles pays where every compute
+        // unit gets a workgroup; smaller batches take the two-tile form (two
+        // waves per SIMD), which starts and drains faster
+        ma.four_tiles = (cn + kQPerBlock - 1) / kQPerBlock >= c->cus;
+        GatherArgs ga{N, c->len_slot, qa, c->d_dep_bf16, w.X, ldq};
+        HWR_HIP(c, timed(c, HWR_K_GATHER, [&] { return launch_gather(ga, c->stream); }));
+        ma.X = w.X;
+        ma.cand_ttft = w.ctt;
+        ma.cand_tpot = w.ctp;
+        ma.cand_nout = w.cno;
+        HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_bf16(c->H, ma, c->stream); }));
         EpilogueArgs ea{};
         ea.N = N;
         ea.M = M;
@@ -1393,10 +1449,10 @@ hwr_status check_route_args(hwr_ctx *c, const hwr_query_batch *q, const hwr_rout
 }
 
 // Work space carved out of this device's static scratch: the predictor table
-// (fused) first, then per chunk row the quality row, the per-candidate
-// predictions (staged and fp32 routes) and the staged features, each block
-// 256-byte aligned.  Chunks hold as many queries as fit, at most max_chunk;
-// 0 rows: one query does not fit.
+// (fused) or the owners of the lengths (fp32) first, then per chunk row the
+// quality row and the table row (fp32) or the per-candidate predictions and
+// the features (staged), each block 256-byte aligned.  Chunks hold as many
+// queries as fit, at most max_chunk; 0 rows: one query does not fit.
 Workspace scratch_workspace(const hwr_ctx *c) {
     Workspace w;
     w.timing = false;
@@ -1405,8 +1461,9 @@ Workspace scratch_workspace(const hwr_ctx *c) {
     const bool staged = c->bf16 && c->pipeline == HWR_PIPE_STAGED;
     auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t entries = fused ? static_cast<size_t>(c->len_rows) * table_stride(c->N) : 0;
-    const size_t fixed = up(entries * 8) + (c->NH == 3 ? up(entries * 4) : 0);
-    const size_t row = M * 4 + (fused ? 0 : N * 4 * (c->NH == 3 ? 3 : 2)) + (staged ? N * kFeatPad * 2 : 0);
+    const size_t fixed = up(entries * 8) + (c->NH == 3 ? up(entries * 4) : 0) + (c->bf16 ? 0 : kOwnLens * sizeof(int32_t));
+    const size_t pairs = c->bf16 ? N : table_stride(c->N);
+    const size_t row = M * 4 + (fused ? 0 : pairs * 4 * (c->NH == 3 ? 3 : 2)) + (staged ? N * kFeatPad * 2 : 0);
     // alignment of the per-row blocks, and the pair-major rows padded to
     // pair_stride(rows) (at most kPairAlign - 1 more rows)
     const size_t slack = 5 * 256 + (kPairAlign - 1) * row;
@@ -1426,7 +1483,12 @@ Workspace scratch_workspace(const hwr_ctx *c) {
         if (c->NH == 3) w.tab_nout = reinterpret_cast<float *>(take(entries * 4));
     }
     w.qmat = reinterpret_cast<float *>(take(rows * M * 4));
-    if (!fused) {
+    if (!c->bf16) {
+        w.owner = reinterpret_cast<int32_t *>(take(kOwnLens * sizeof(int32_t)));
+        w.tab = reinterpret_cast<float *>(take(rows * pairs * 8));
+        if (c->NH == 3) w.tab_nout = reinterpret_cast<float *>(take(rows * pairs * 4));
+    }
+    if (staged) {
         w.ctt = reinterpret_cast<float *>(take(ldq * N * 4));
         w.ctp = reinterpret_cast<float *>(take(ldq * N * 4));
         if (c->NH == 3) w.cno = reinterpret_cast<float *>(take(ldq * N * 4));

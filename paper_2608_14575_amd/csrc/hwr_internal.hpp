@@ -139,7 +139,7 @@ struct QualityArgs {
     int nq, D, M;
     const void *emb;              // [nq][D] (bf16 bits or fp32)
     const uint16_t *wq_pk;        // bf16 B-operand fragments
-    const float *wq;              // fp32 [D][M]
+    const float *wq;              // fp32 B operands (pack_quality_f32)
     const float *bq;              // [M]
     float *qmat;                  // [nq][M]
 };
@@ -190,23 +190,30 @@ struct RouteArgs {
     QueryArgs q;
     const int32_t *dep_model;
     const float *tab, *tab_nout;  // as in TableArgs; tab_nout null: the query's given N_out
-    const uint16_t *len_row;      // [kLenBits] table row by feature bits (len_index), or null: row = query
+    const uint16_t *len_row;      // [kLenBits] table row by feature bits (len_index), or null:
+    const int32_t *owner;         // [kOwnLens] row of a query's length (fp32), or null: row = query
     QualityArgs quality;
     float *dbg_ttft, *dbg_tpot, *dbg_nout;   // caller's per-candidate outputs [nq][N], or null
     OutArgs out;
 };
 
-struct MlpF32Args {
-    int N, F, len_slot, nheads;
+// fp32 predictor: a query of a length below kOwnLens may share its row of the
+// table with the chunk's other queries of that length (owner[length]).
+constexpr int kOwnLens = 1 << 16;
+struct F32Predictor {
+    const float *packed;          // F32Weights<H> (pack_predictor_f32)
     float b3_0, b3_1, b3_2;
+};
+struct MlpF32Args {
+    int N, ldn, len_slot, nheads;
+    int kq;                       // layer-1 k-steps / 4: 1 (no feature past slot 15) or 2
     QueryArgs q;
     const float *dep_f32;         // [N][32]
-    const float *w1, *b1, *w2, *b2, *w3;   // [F][H], [H], [H][H], [H], [H][nheads]
-    float *cand_ttft, *cand_tpot, *cand_nout;   // [N][ldq], pair-major; cand_nout: three heads only
-    int ldq;                      // pair_stride(nq)
-    int with_quality;             // workgroups past mlp_blocks run `quality`
-    int mlp_blocks;               // set by launch_mlp_f32
-    QualityArgs quality;
+    F32Predictor p;
+    const int32_t *owner;         // [kOwnLens] (k_mlp_f32)
+    float *tab, *tab_nout;        // [nq][ldn][2], [nq][ldn]: rows by query
+    int mlp_blocks;               // set by launch_mlp_f32_small
+    QualityArgs quality;          // launch_mlp_f32_small
 };
 
 struct GatherArgs {
@@ -275,15 +282,18 @@ struct SingleArgs {
 hipError_t launch_state(const StateArgs &a, hipStream_t s);
 // cus: compute units of the device (a grid below it takes the unrolled variant)
 hipError_t launch_quality_bf16(const QualityArgs &a, int cus, hipStream_t s);
-hipError_t launch_quality_f32(const QualityArgs &a, hipStream_t s);
+// fp32: qualities, and (owner not null) the owners of the chunk's lengths
+hipError_t launch_quality_f32(const QualityArgs &a, const int32_t *input_len, int32_t *owner, hipStream_t s);
 hipError_t launch_mlp_bf16(int H, const MlpArgs &a, hipStream_t s);   // staged
 // Table of a.rows x a.N predictions; with a.quality.nq > 0 the same launch runs
 // the quality tiles beside it, in workgroups of their own.
 hipError_t launch_table(int H, const TableArgs &a, int cus, hipStream_t s);
 // Decisions; with_quality: the quality GEMM inside, else from a.quality.qmat.
 hipError_t launch_route(const RouteArgs &a, bool with_quality, hipStream_t s);
-int mlp_f32_blocks(long candidates);   // workgroups of launch_mlp_f32's predictor
-hipError_t launch_mlp_f32(int H, const MlpF32Args &a, hipStream_t s);
+int mlp_f32_small_blocks(int nq, int N);   // workgroups of launch_mlp_f32_small
+int quality_f32_blocks(int nq);
+hipError_t launch_mlp_f32_small(int H, const MlpF32Args &a, hipStream_t s);   // with the qualities
+hipError_t launch_mlp_f32(int H, const MlpF32Args &a, int cus, hipStream_t s);   // rows of owning queries
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
 hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s);
 hipError_t launch_single(int H, bool resident, const SingleArgs &a, hipStream_t s);

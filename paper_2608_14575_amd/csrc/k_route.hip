@@ -77,7 +77,8 @@ __global__ __launch_bounds__(kRouteThreads) void k_route(RouteArgs a) {
             s_len[tid] = len;
             s_nout[tid] = static_cast<float>(no < 0 ? 0 : no);
             s_slo[tid] = a.q.slo ? a.q.slo[q] : a.q.default_slo;
-            s_row[tid] = a.len_row ? a.len_row[len_index(bf16_bits(len_feature(len)))] : q;
+            if (a.len_row) s_row[tid] = a.len_row[len_index(bf16_bits(len_feature(len)))];
+            else s_row[tid] = a.owner && static_cast<uint32_t>(len) < static_cast<uint32_t>(kOwnLens) ? a.owner[len] : q;
         }
         for (int i = tid; i < N; i += kRouteThreads) s_model[i] = static_cast<uint8_t>(a.dep_model[i]);
     };

@@ -1,0 +1,62 @@
+"""fp32 path: the batch form of the predictor (one row per distinct input
+length) against the small-batch form (every candidate) bit for bit, and both
+against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2608_14575_amd import hwr
+from paper_2608_14575_amd import synth as S
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,heads,models,gpus,gw,D", [
+    (64, 2, 4, 2, 3, 64), (128, 3, 5, 3, 3, 192), (64, 3, 17, 1, 8, 320), (128, 2, 32, 2, 8, 128)])
+def test_rows_by_length_equal_every_candidate(hidden, heads, models, gpus, gw, D):
+    """1,300 queries, lengths repeated, on both sides of the length the owner
+    table ends at, and huge; one and two model tiles; features within and past
+    slot 16.  One chunk lists more queries than compute units; chunks of at most
+    eight take the small form."""
+    sp = S.spec("C1", n_queries=1300, hidden=hidden, n_heads=heads, n_models=models, n_gpu_types=gpus, gpu_width=gw,
+                feat_dim=32 if gw > 3 else 24, embed_dim=D)
+    pb, st, qs = S.make_problem(sp, 3), S.make_state(sp, 3), S.make_queries(sp, 3)
+    r = np.random.default_rng(4)
+    qs.input_len[:] = r.choice(np.concatenate([np.arange(1, 120), [65534, 65535, 65536, 65537, 70000, 2**31 - 1]]), 1300)
+    small = 8 if models < 32 else 4
+    outs = []
+    for chunk in (1300, 600, small):
+        ro = G.make_router(pb, max_chunk=chunk)
+        ro.update(st)
+        ro.profile(True)
+        outs.append(G.route_device(ro, qs, "f32"))
+        assert (ro.profile_read(reset=True)["quality"][1] == 0) == (chunk == small)
+        ro.close()
+    for o in outs[1:]:
+        for k in o:
+            assert o[k].tobytes() == outs[0][k].tobytes(), k
+    idx = np.arange(0, 1300, 5)
+    rep = G.check(pb, st, qs.take(idx), {k: v[idx] for k, v in outs[0].items()}, query_ids=idx)
+    print(rep.summary(), flush=True)
+    assert rep.ok, rep.failures[:5]
+    assert rep.max_rel_ttft < 1e-5 and rep.max_rel_tpot < 1e-5
+
+
+@pytest.mark.parametrize("n", [5, 700])
+def test_embeddings_at_any_float_address(n):
+    """Embeddings 4 bytes off a 16-byte boundary give the same outputs."""
+    import torch
+    sp = S.spec("C1", n_queries=n)
+    pb, st, qs = S.make_problem(sp, 5), S.make_state(sp, 5), S.make_queries(sp, 5)
+    r = G.make_router(pb)
+    r.update(st)
+    ref = G.route_device(r, qs, "f32", candidates=False)
+    emb, il, no, slo = G.to_dev_inputs(qs, "f32")
+    off = torch.empty(emb.numel() + 1, device="cuda")
+    off[1:] = emb.reshape(-1)
+    out = G.dev_outputs(n, r.N, r.M, False)
+    r.route(off[1:].view(n, -1), il, no, slo, mem=hwr.HWR_MEM_DEVICE, **out)
+    torch.cuda.synchronize()
+    for k in out:
+        assert out[k].cpu().numpy().tobytes() == ref[k].tobytes(), k
