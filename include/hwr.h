@@ -210,7 +210,8 @@ hwr_status hwr_init(const hwr_config *cfg, hwr_ctx **out);
 hwr_status hwr_update_hw_state(hwr_ctx *ctx, const hwr_hw_state *state, int32_t n);
 
 /* Route a batch (Eq. 3 for each query).  n == 0 is a no-op.  Batches larger
- * than max_chunk run as successive chunks on the context's stream.  A single
+ * than max_chunk run as successive chunks on the context's stream (in one launch
+ * where the chunks need no work space: see HWR_K_FUSED below).  A single
  * query in host memory takes a latency path: one kernel launch (or, with
  * HWR_FLAG_GRAPH, one launch of a graph holding that kernel, captured on the
  * first call; on ROCm 7 such a launch is about 5 us faster with the runtime's
@@ -259,7 +260,8 @@ const char *hwr_last_error(const hwr_ctx *ctx);
  * The fused pipeline's decisions are HWR_K_FUSED.  Its predictor table runs
  * inside the quality launch (HWR_K_QUALITY) on small chunks; chunks of 64
  * queries per compute unit or more compute the qualities inside the decision
- * kernel instead (no HWR_K_QUALITY), and the table is HWR_K_MLP.  fp32 chunks
+ * kernel instead (no HWR_K_QUALITY), all chunks of the batch in one launch, and
+ * the table is HWR_K_MLP.  fp32 chunks
  * small enough for the predictor and the quality rows to share the device run
  * both in the predictor's launch: HWR_K_MLP, no HWR_K_QUALITY.  HWR_K_MERGE is
  * kept for its index; no kernel reports it.

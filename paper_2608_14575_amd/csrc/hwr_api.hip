@@ -935,9 +935,13 @@ hwr_status route_f32(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, con
         HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_mlp_f32(c->H, fa, c->cus, c->stream); }));
         ra.owner = w.owner;
     }
-    HWR_HIP(c, timed(c, HWR_K_EPILOGUE, [&] { return launch_route(ra, false, c->stream); }));
+    HWR_HIP(c, timed(c, HWR_K_EPILOGUE, [&] { return launch_route(ra, false, c->cus, c->stream); }));
     return HWR_OK;
 }
+
+// Whether a chunk of the fused pipeline gives every compute unit a 64-query
+// workgroup of the decision kernel, which then computes the qualities itself.
+bool quality_inside(const hwr_ctx *c, int cn) { return (cn + 63) / 64 >= c->cus; }
 
 // One chunk of the fused pipeline.  Chunks that give every compute unit a
 // 64-query workgroup compute the qualities inside the decision kernel, which
@@ -962,8 +966,8 @@ hwr_status route_fused(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, c
     ta.tab_nout = w.tab_nout;
     RouteArgs ra = route_args(c, qu, qa, oa, w, ctt, ctp, cno);
     ra.len_row = by_value ? c->d_len_row : nullptr;
-    const bool quality_inside = (cn + 63) / 64 >= c->cus;
-    if (quality_inside) {
+    const bool inside = quality_inside(c, cn);
+    if (inside) {
         if (need_table) HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_table(c->H, ta, c->cus, c->stream); }));
         if (!want_quality) ra.quality.qmat = nullptr;
     } else {
@@ -973,7 +977,7 @@ hwr_status route_fused(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, c
             return launch_table(c->H, ta, c->cus, c->stream);
         }));
     }
-    HWR_HIP(c, timed(c, HWR_K_FUSED, [&] { return launch_route(ra, quality_inside, c->stream); }));
+    HWR_HIP(c, timed(c, HWR_K_FUSED, [&] { return launch_route(ra, inside, c->cus, c->stream); }));
     return HWR_OK;
 }
 
@@ -993,8 +997,13 @@ hwr_status route_device(hwr_ctx *c, const DevBatch &b, const Workspace &w) {
     // pair) when the batch has no more queries than the feature has values
     // (fewer evaluations either way); the values' table serves every chunk.
     const bool by_value = fused && b.n > c->len_rows;
-    for (int off = 0; off < b.n; off += w.max_chunk) {
-        const int cn = std::min(w.max_chunk, b.n - off);
+    // Chunks whose decision kernel computes the qualities itself use no work
+    // space but the table: they are routed together, in one launch (up to the
+    // kernels' 32-bit output indexes).
+    const int chunk = by_value && quality_inside(c, std::min(w.max_chunk, b.n)) ? std::max(w.max_chunk, INT32_MAX / kMaxWeights)
+                                                                               : w.max_chunk;
+    for (int off = 0; off < b.n; off += chunk) {
+        const int cn = std::min(chunk, b.n - off);
         const int ldq = pair_stride(cn);       // pair-major row stride of this chunk
         QueryArgs qa;
         qa.nq = cn;

@@ -136,11 +136,18 @@ __device__ inline Bound make_bound(float slo) {
 // Dev. 34(1), 1990; Muller et al., Handbook of Floating-Point Arithmetic,
 // division by FMA).  The ranges keep every step clear of underflow and
 // overflow; outside them the plain IEEE division is used.
-__device__ inline float div_bound(float c, const Bound &b) {
+__device__ inline float div_bound_fast(float c, const Bound &b) {
     const float q0 = __fmul_rn(c, b.rcp);
     const float r = __fmaf_rn(-q0, b.slo, c);
-    float t = __fmaf_rn(r, b.rcp, q0);
-    if (!(b.fast && c >= 0x1p-60f && c <= 0x1p60f)) {
+    return __fmaf_rn(r, b.rcp, q0);
+}
+// Whether div_bound_fast applies to every cost in [lo, hi].
+__device__ inline bool div_in_range(float lo, float hi, const Bound &b) {
+    return b.fast && lo >= 0x1p-60f && hi <= 0x1p60f;
+}
+__device__ inline float div_bound(float c, const Bound &b) {
+    float t = div_bound_fast(c, b);
+    if (!div_in_range(c, c, b)) {
         asm volatile("");         // a real branch: keeps the division off the common path
         t = __fdiv_rn(c, b.slo);
     }

@@ -289,7 +289,7 @@ hipError_t launch_mlp_bf16(int H, const MlpArgs &a, hipStream_t s);   // staged
 // the quality tiles beside it, in workgroups of their own.
 hipError_t launch_table(int H, const TableArgs &a, int cus, hipStream_t s);
 // Decisions; with_quality: the quality GEMM inside, else from a.quality.qmat.
-hipError_t launch_route(const RouteArgs &a, bool with_quality, hipStream_t s);
+hipError_t launch_route(const RouteArgs &a, bool with_quality, int cus, hipStream_t s);
 int mlp_f32_small_blocks(int nq, int N);   // workgroups of launch_mlp_f32_small
 int quality_f32_blocks(int nq);
 hipError_t launch_mlp_f32_small(int H, const MlpF32Args &a, hipStream_t s);   // with the qualities

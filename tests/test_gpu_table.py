@@ -111,3 +111,30 @@ def test_utilities_without_an_order(n):
     out = _both(sp, 8, n, edit)
     assert (out["choice"] >= 0).all() and (out["choice"] < 27).all()
     assert 0.0 < out["feasible"].mean() < 1.0
+
+
+@pytest.mark.parametrize("n", [300, 17001])
+@pytest.mark.parametrize("models,gpus", [(1, 1), (2, 1), (7, 1), (5, 3), (16, 1), (17, 1), (21, 3), (32, 2), (13, 5), (31, 3), (16, 8)])
+def test_pair_counts(models, gpus, n):
+    """Lanes take pairs in steps of 16 and groups of 64: one pair, odd counts on
+    both sides of a step and of a group, whole groups; the last pair's
+    neighbour in a table row is padding.  Small batches and streaming ones."""
+    sp = S.spec("C2", n_models=models, n_gpu_types=gpus, hidden=64, embed_dim=192, gpu_width=8, feat_dim=32)
+    kw = dict(cost_weights=[0.0, 0.6, 1.7]) if gpus == 3 else {}
+    _both(sp, 9, n, candidates=n < 1000, **kw)
+
+
+@pytest.mark.parametrize("embed_dim", [128, 192])
+def test_streaming_chunks_are_one_launch(embed_dim):
+    """A batch whose chunks would each fill the device is routed in one launch:
+    the same bits as the staged pipeline in chunks, several tiles to a wave (the
+    last one ragged), candidates and qualities included."""
+    sp = S.spec("C2", n_models=9, n_gpu_types=3, hidden=64, embed_dim=embed_dim)
+    _both(sp, 10, 200_003, max_chunk=16_500)
+    r = G.make_router(S.make_problem(sp, 10), max_chunk=16_500)
+    r.update(S.make_state(sp, 10))
+    r.profile(True)
+    G.route_device(r, S.make_queries(sp, 10, n=40_000), "bf16", candidates=False)
+    kt = r.profile_read(reset=True)
+    r.close()
+    assert kt["fused"][1] == 1 and kt["quality"][1] == 0 and kt["mlp"][1] == 1
