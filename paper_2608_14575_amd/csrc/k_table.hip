@@ -21,6 +21,71 @@ namespace hwr {
 constexpr int kTableWaves = 8;                    // two per SIMD
 constexpr int kTableThreads = 64 * kTableWaves;
 
+// Quality tiles of a workgroup of their own, RT of them (32 queries each): all
+// eight waves fetch the rows and the weights of 512 k into LDS, with the next 512
+// k already requested, so that one trip to memory covers D <= 1,024; wave i < RT
+// multiplies tile i (quality_tile's chain: same bits).  A lone wave per tile
+// (quality_tile) waits for memory once per 256 k: the
+// call at 4,096 x 16, D = 768 11.15 -> 10.42 us, at 8,192 x 48 15.9 -> 15.2, at 1,003
+// x 91 10.87 -> 10.62.  More tiles to a workgroup keep a wave each: their loads
+// already overlap, and one or two waves multiplying for all would be the longer
+// chain.
+constexpr int kCoopK = 512, kCoopRow = 2 * kCoopK + 16;    // 16-byte pad: rows in different banks
+constexpr int kCoopTiles = 2;                              // at most: the loads held per thread
+constexpr int kCoopBytes = 32 * kCoopTiles * kCoopRow + kCoopK * 64;
+template <int RT>
+__device__ __forceinline__ void quality_tiles_coop(const QualityArgs &a, int q0, unsigned char *lds) {
+    constexpr int T = kTableThreads, PPR = 2 * kCoopK / 16;
+    constexpr int NE = 32 * RT * PPR / T, NQ = kCoopK * 4 / T;   // 16-byte pieces per thread: rows, weights
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 31, h = lane >> 5, S = a.D / 64, chunks = (a.D + kCoopK - 1) / kCoopK;
+    const uint16_t *emb = static_cast<const uint16_t *>(a.emb);
+    const u32x4 *wq = reinterpret_cast<const u32x4 *>(a.wq_pk);
+    unsigned char *lds_w = lds + 32 * RT * kCoopRow;
+    u32x4 e[NE], w[NQ];
+    // past the queries, a row's end or the weights: the last piece, never used
+    auto load = [&](int j) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int p = tid + T * i, q = min(q0 + p / PPR, a.nq - 1), k = min(j * kCoopK + p % PPR * 8, a.D - 8);
+            e[i] = *reinterpret_cast<const u32x4 *>(emb + static_cast<size_t>(q) * a.D + k);
+        }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) w[i] = wq[min(j * kCoopK * 4 + tid + T * i, a.D * 4 - 1)];
+    };
+    f32x16 acc = {};
+    load(0);
+    for (int j = 0; j < chunks; ++j) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int p = tid + T * i;
+            *reinterpret_cast<u32x4 *>(lds + p / PPR * kCoopRow + p % PPR * 16) = e[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) *reinterpret_cast<u32x4 *>(lds_w + (tid + T * i) * 16) = w[i];
+        if (j + 1 < chunks) load(j + 1);
+        __syncthreads();
+        if (wave < RT) {
+            const unsigned char *base = lds + (32 * wave + row) * kCoopRow + 64 * h;
+            const int slices = min(kCoopK / 64, S - j * (kCoopK / 64));
+            for (int sl = 0; sl < slices; ++sl)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc = mfma32(*reinterpret_cast<const bf16x8 *>(base + 128 * sl + 16 * c),
+                                 *reinterpret_cast<const bf16x8 *>(lds_w + ((sl * 4 + c) * 64 + lane) * 16), acc);
+        }
+        __syncthreads();
+    }
+    if (wave < RT && row < a.M) {
+        const float bias = a.bq[row];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int q = q0 + 32 * wave + crow(r, h);
+            if (q < a.nq) a.qmat[static_cast<size_t>(q) * a.M + row] = acc[r] + bias;
+        }
+    }
+}
+
 // A wave evaluates 64 consecutive (row, pair) entries per step, two 32-column
 // tiles whose columns may lie in any rows: no padding but the last step's.  A
 // step's cost is its MFMA chain (H = 256: 288 32x32x16 MFMAs, about 9,300
@@ -30,10 +95,15 @@ constexpr int kTableThreads = 64 * kTableWaves;
 // (HBM-bound, and independent of the table) at the same time.
 template <int H, int NH, bool FB>
 __global__ __launch_bounds__(kTableThreads, 1) void k_table(TableArgs a) {
-    __shared__ PredictorLds<H, NH> s;
+    constexpr int kLds = sizeof(PredictorLds<H, NH>) > kCoopBytes ? sizeof(PredictorLds<H, NH>) : kCoopBytes;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+    PredictorLds<H, NH> &s = *reinterpret_cast<PredictorLds<H, NH> *>(lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (static_cast<int>(blockIdx.x) >= a.blocks) {
-        const int q0 = ((blockIdx.x - a.blocks) * a.qual_waves + wave) * 32;
+        const int first = (blockIdx.x - a.blocks) * a.qual_waves * 32;
+        if (a.qual_waves == 1) return quality_tiles_coop<1>(a.quality, first, lds);
+        if (a.qual_waves == kCoopTiles) return quality_tiles_coop<kCoopTiles>(a.quality, first, lds);
+        const int q0 = first + wave * 32;
         if (wave < a.qual_waves && q0 < a.quality.nq) quality_tile<4>(a.quality, q0, lane);
         return;
     }

@@ -138,3 +138,12 @@ def test_streaming_chunks_are_one_launch(embed_dim):
     kt = r.profile_read(reset=True)
     r.close()
     assert kt["fused"][1] == 1 and kt["quality"][1] == 0 and kt["mlp"][1] == 1
+
+
+@pytest.mark.parametrize("embed_dim", [64, 576, 1088])
+@pytest.mark.parametrize("n", [20, 1003, 4097, 5000, 9000])
+def test_quality_tiles_beside_the_table(embed_dim, n):
+    """One, two and three quality tiles to a workgroup (the first two fetched by
+    the whole workgroup, 512 k at a time), the last workgroups with few or no
+    queries; less than 512 k, a partial second and third."""
+    _both(S.spec("C2", n_models=5, n_gpu_types=2, hidden=64, embed_dim=embed_dim), 11, n)
