@@ -52,10 +52,12 @@
  *    query and result buffers.  Configuration and state are copied in.
  *  - HWR_MEM_DEVICE batches are ordered on the context's stream and return
  *    without waiting; HWR_MEM_HOST batches return with the results written.
- *    A host batch larger than max_chunk is streamed: the next chunk's upload
+ *    A host batch of at most max_chunk queries without per-candidate outputs
+ *    passes through pinned memory of the context (grown on demand, up to 8 MB,
+ *    held until hwr_free); a larger one is streamed: the next chunk's upload
  *    (on a second stream of the context) overlaps this chunk's kernels.  A
  *    host batch in pageable memory with 16 MB of embeddings or more is copied
- *    through 128 MB of pinned memory the context allocates on first use, by
+ *    through 32 MB of pinned memory the context allocates on first use, by
  *    up to seven host threads of its own (held until hwr_free).
  *  - A context is not thread-safe: one context per thread (or per stream).
  */

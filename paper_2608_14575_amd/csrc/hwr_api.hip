@@ -72,9 +72,22 @@ void *g_scratch_ptr[kMaxDevices] = {};
 // pinned slots, each filled by a few host threads while the previous one is
 // uploaded (the runtime's own staging of a pageable copy runs on one thread,
 // at about half the rate of an upload from pinned memory).
+// Small slots: the first fill and the last upload overlap nothing, and the ring
+// costs less to pin.  41 MB: 32 MB slots 1,310 us, 16 and 8 MB about 1,000-1,070, 4 MB
+// 1,025, 2 MB 1,320.
 constexpr int kPageSlots = 4;
-constexpr size_t kPageSlotBytes = size_t(32) << 20;
+constexpr size_t kPageSlotBytes = size_t(8) << 20;
 constexpr size_t kPageMinBytes = size_t(16) << 20;   // smaller batches keep the runtime's copy
+
+// Host batches of one chunk: everything but large embeddings passes through one
+// pinned block, which the device reads and writes itself or takes in one copy
+// (a pageable copy of a few KB costs the host about 15 us, and a batch has
+// eleven): 24 x 32, D = 768: 170 -> 37 us.  Up to kPackRead bytes of inputs are
+// read over the bus by the kernels, more go up in one copy first: 241 KB take
+// 41.9 us read and 47.3 copied, 967 KB 73.1 and 74.7.
+constexpr size_t kPackEmb = size_t(1) << 20;      // larger embeddings go up by themselves
+constexpr size_t kPackMax = size_t(8) << 20;      // lengths, bounds and outputs; larger batches: the chunk path
+constexpr size_t kPackRead = size_t(1) << 20;
 
 // A few threads that copy one host range into another together with the
 // calling thread; one copy at a time (a context is used by one thread).
@@ -238,6 +251,10 @@ struct hwr_ctx {
         bool used = false;
     } pslot[kPageSlots];
     int pslot_next = 0;
+    // pinned block of single-chunk host batches, its device address, and the
+    // device copies of its inputs and of large embeddings
+    unsigned char *h_pack = nullptr, *d_pack = nullptr, *pack_in = nullptr, *pack_emb = nullptr;
+    size_t pack_cap = 0, pack_in_cap = 0, pack_emb_cap = 0;
     std::unique_ptr<CopyPool> copier;  // set up by the first pageable host batch
     bool page_failed = false;          // the pinned ring could not be set up: the runtime copies
     int32_t *d_hchoice = nullptr;
@@ -631,7 +648,7 @@ void release(hwr_ctx *c) {
                         c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno, c->d_X, c->d_tab,
                         c->d_tab_nout, c->d_len_row, c->hin[0].emb, c->hin[0].len, c->hin[0].nout, c->hin[0].slo,
                         c->hin[1].emb, c->hin[1].len, c->hin[1].nout, c->hin[1].slo, c->d_hchoice,
-                        c->d_hval, c->d_hcand, c->d_hqual, c->d_hfeas};
+                        c->d_hval, c->d_hcand, c->d_hqual, c->d_hfeas, c->pack_in, c->pack_emb};
     if (c->cstream) (void)hipStreamSynchronize(c->cstream);
     for (void *p : dev_ptrs)
         if (p) (void)hipFree(p);
@@ -645,6 +662,7 @@ void release(hwr_ctx *c) {
         if (sl.buf) (void)hipHostFree(sl.buf);
         if (sl.done) (void)hipEventDestroy(sl.done);
     }
+    if (c->h_pack) (void)hipHostFree(c->h_pack);
     if (c->h_ring) (void)hipHostFree(c->h_ring);
     if (c->h_cur) (void)hipHostFree(c->h_cur);
     if (c->sstream) (void)hipStreamDestroy(c->sstream);
@@ -1137,7 +1155,7 @@ hwr_status ensure_host_staging(hwr_ctx *c, size_t rows) {
 // the host stages itself) the host stages chunk i + 1 while the device
 // computes chunk i.  Returns when every output is in host memory, or, on an
 // error, once both streams have drained.
-hwr_status route_host_chunks(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r);
+hwr_status route_host_chunks(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r, HostMem em);
 
 // The pinned ring and the copy threads of pageable host batches, set up once.
 // When pinned memory cannot be had, pageable batches keep the runtime's copy.
@@ -1190,8 +1208,115 @@ hwr_status upload_pageable(hwr_ctx *c, void *dst, const void *src, size_t bytes,
     return HWR_OK;
 }
 
+// Grow-only device buffer (idle: every host batch ends with its stream).
+hwr_status grow_dev(hwr_ctx *c, unsigned char **p, size_t *cap, size_t bytes) {
+    if (bytes <= *cap) return HWR_OK;
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
+    *cap = 0;
+    HWR_HIP(c, hipMalloc(reinterpret_cast<void **>(p), bytes));
+    *cap = bytes;
+    return HWR_OK;
+}
+
+// Layout of the pinned block: inputs, then outputs, each array 256-byte aligned.
+struct HostPack {
+    size_t emb = 0, len = 0, nout = 0, slo = 0, inputs = 0, choice = 0, feasible = 0, val[5] = {}, total = 0;
+};
+HostPack host_pack(const hwr_ctx *c, const hwr_query_batch *q, size_t emb_bytes) {
+    HostPack k;
+    auto take = [&](size_t bytes) {
+        const size_t at = k.total;
+        k.total = (k.total + bytes + 255) & ~size_t(255);
+        return at;
+    };
+    const size_t n = static_cast<size_t>(q->n), on = n * c->nw;
+    k.emb = take(emb_bytes <= kPackEmb ? emb_bytes : 0);
+    k.len = take(n * 4);
+    k.nout = take(c->NH == 2 ? n * 4 : 0);
+    k.slo = take(q->slo_s ? n * 4 : 0);
+    k.inputs = k.total;
+    k.choice = take(on * 4);
+    k.feasible = take(on);
+    for (size_t &v : k.val) v = take(on * 4);
+    return k;
+}
+
+// Whether a host batch goes through the pinned block: one chunk, no
+// per-candidate outputs, results in plain host memory (the host writes them).
+bool packable(const hwr_ctx *c, const hwr_query_batch *q, const hwr_route_result *r, const HostPack &k) {
+    if (q->n > c->max_chunk || k.total > kPackMax || r->cand_ttft || r->cand_tpot || r->cand_nout || r->cand_quality)
+        return false;
+    const void *outs[] = {r->choice, r->feasible, r->utility, r->e2e_s, r->ttft_s, r->tpot_s, r->nout};
+    for (const void *o : outs)
+        if (o && host_mem(o) == HostMem::kDevice) return false;
+    return true;
+}
+
+hwr_status route_host_packed(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r, const HostPack &k, HostMem em) {
+    const size_t n = static_cast<size_t>(q->n), on = n * c->nw;
+    const size_t emb_bytes = n * c->D * (c->bf16 ? 2 : 4);
+    hipStream_t s = c->stream;
+    if (k.total > c->pack_cap) {
+        if (c->h_pack) (void)hipHostFree(c->h_pack);
+        c->h_pack = c->d_pack = nullptr;
+        c->pack_cap = 0;
+        HWR_HIP(c, hipHostMalloc(reinterpret_cast<void **>(&c->h_pack), k.total, hipHostMallocMapped));
+        HWR_HIP(c, hipHostGetDevicePointer(reinterpret_cast<void **>(&c->d_pack), c->h_pack, 0));
+        c->pack_cap = k.total;
+    }
+    const unsigned char *in = c->d_pack, *emb = nullptr;
+    if (k.inputs > kPackRead) {
+        const hwr_status st = grow_dev(c, &c->pack_in, &c->pack_in_cap, k.inputs);
+        if (st != HWR_OK) return st;
+        in = c->pack_in;
+    }
+    unsigned char *h = c->h_pack;
+    std::memcpy(h + k.len, q->input_len, n * 4);
+    if (c->NH == 2) std::memcpy(h + k.nout, q->expected_out_len, n * 4);
+    if (q->slo_s) std::memcpy(h + k.slo, q->slo_s, n * 4);
+    if (emb_bytes <= kPackEmb) {
+        std::memcpy(h + k.emb, q->emb, emb_bytes);
+        emb = in + k.emb;
+    }
+    if (k.inputs > kPackRead) HWR_HIP(c, hipMemcpyAsync(c->pack_in, h, k.inputs, hipMemcpyHostToDevice, s));
+    if (!emb) {
+        hwr_status st = grow_dev(c, &c->pack_emb, &c->pack_emb_cap, emb_bytes);
+        if (st != HWR_OK) return st;
+        if (emb_bytes >= kPageMinBytes && em == HostMem::kPageable && page_ring(c)) {
+            st = upload_pageable(c, c->pack_emb, q->emb, emb_bytes, s);
+            if (st != HWR_OK) return st;
+        } else {
+            HWR_HIP(c, hipMemcpyAsync(c->pack_emb, q->emb, emb_bytes, hipMemcpyHostToDevice, s));
+        }
+        emb = c->pack_emb;
+    }
+    DevBatch b{};
+    b.n = q->n;
+    b.emb = emb;
+    b.len = reinterpret_cast<const int32_t *>(in + k.len);
+    b.nout = reinterpret_cast<const int32_t *>(in + k.nout);
+    b.slo = q->slo_s ? reinterpret_cast<const float *>(in + k.slo) : nullptr;
+    auto val = [&](int i, const float *want) { return want ? reinterpret_cast<float *>(c->d_pack + k.val[i]) : nullptr; };
+    b.out = OutArgs{reinterpret_cast<int32_t *>(c->d_pack + k.choice), r->feasible ? c->d_pack + k.feasible : nullptr,
+                    val(0, r->utility), val(1, r->e2e_s), val(2, r->ttft_s), val(3, r->tpot_s), val(4, r->nout)};
+    const hwr_status st = route_device(c, b, ctx_workspace(c));
+    if (st != HWR_OK) return st;
+    HWR_HIP(c, hipStreamSynchronize(s));
+    std::memcpy(r->choice, h + k.choice, on * 4);
+    if (r->feasible) std::memcpy(r->feasible, h + k.feasible, on);
+    float *vals[5] = {r->utility, r->e2e_s, r->ttft_s, r->tpot_s, r->nout};
+    for (int i = 0; i < 5; ++i)
+        if (vals[i]) std::memcpy(vals[i], h + k.val[i], on * 4);
+    return HWR_OK;
+}
+
 hwr_status route_host(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r) {
-    const hwr_status st = route_host_chunks(c, q, r);
+    const size_t emb_bytes = static_cast<size_t>(q->n) * c->D * (c->bf16 ? 2 : 4);
+    const HostMem em = host_mem(q->emb);
+    if (em == HostMem::kDevice) return fail(c, HWR_ERR_INVALID_ARG, "HWR_MEM_HOST batch with a device pointer");
+    const HostPack k = host_pack(c, q, emb_bytes);
+    const hwr_status st = packable(c, q, r, k) ? route_host_packed(c, q, r, k, em) : route_host_chunks(c, q, r, em);
     if (st != HWR_OK) {
         // copies may still read the caller's buffers or write its results:
         // let both streams drain before the caller gets control back
@@ -1201,7 +1326,7 @@ hwr_status route_host(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r)
     return st;
 }
 
-hwr_status route_host_chunks(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r) {
+hwr_status route_host_chunks(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r, HostMem em) {
     const size_t rows = static_cast<size_t>(std::min(q->n, c->max_chunk));
     hwr_status st = ensure_host_staging(c, rows);
     if (st != HWR_OK) return st;
@@ -1209,8 +1334,6 @@ hwr_status route_host_chunks(hwr_ctx *c, const hwr_query_batch *q, hwr_route_res
     const int N = c->N, M = c->M, D = c->D;
     hipStream_t s = c->stream, cs = c->cstream;
     const size_t emb_bytes = static_cast<size_t>(q->n) * D * esz;
-    const HostMem em = host_mem(q->emb);
-    if (em == HostMem::kDevice) return fail(c, HWR_ERR_INVALID_ARG, "HWR_MEM_HOST batch with a device pointer");
     const bool staged_copy = emb_bytes >= kPageMinBytes && em == HostMem::kPageable && page_ring(c);
     auto upload = [&](int off) -> hwr_status {
         const int cn = std::min(c->max_chunk, q->n - off);

@@ -201,7 +201,7 @@ def test_large_host_batches_through_the_pinned_ring(pinned):
     """A pageable host batch of at least 16 MB of embeddings passes through the
     library's pinned ring (filled by its copy threads); a pinned one is
     uploaded directly.  20,000 C3 queries (41 MB) in chunks of 3,000, so the
-    ring of four 32 MB slots wraps, against the device path in one chunk, bit
+    ring of four slots wraps, against the device path in one chunk, bit
     for bit; then a second batch through the same router."""
     import torch
     sp, pb, st, qs = _case("C3", n_queries=20000)
@@ -423,3 +423,27 @@ def test_contexts_on_threads_are_independent():
         assert len(got[i]) == 4
         for out in got[i]:
             _same(out, ref[i])
+
+
+@pytest.mark.parametrize("dtype,n,kw,slo", [
+    ("bf16", 24, {}, False), ("bf16", 677, {}, True), ("bf16", 678, {}, True), ("bf16", 682, dict(cost_weights=[0.1, 0.5, 2.0]), True),
+    ("bf16", 683, dict(cost_weights=[0.1, 0.5, 2.0]), True), ("f32", 100, {}, True), ("f32", 700, {}, True),
+])
+def test_host_batches_of_one_chunk(dtype, n, kw, slo):
+    """Around the sizes where a host batch's inputs are copied to the device
+    before the kernels and where its embeddings go up by themselves (1 MB): the device path's bits, twice through one router, then a smaller
+    batch; optional outputs left out; candidates (another path) included."""
+    sp, pb, st, qs = _case("C2" if dtype == "bf16" else "C1", n_queries=n, embed_dim=768)
+    r = G.make_router(pb, **kw)
+    r.update(st)
+    d = G.route_device(r, qs, sp.dtype, candidates=True, with_slo=slo)
+    emb = qs.emb_bits
+    s = qs.slo_s if slo else None
+    for cand in (False, True, False):
+        h = r.route_host(emb, qs.input_len, qs.expected_out_len, s, candidates=cand)
+        _same({k: d[k] for k in h}, h)
+    h = r.route_host(emb[:33], qs.input_len[:33], qs.expected_out_len[:33], None if s is None else s[:33])
+    _same({k: d[k][:33] for k in h}, h)
+    out = np.full(d["choice"].shape, -1, np.int32)
+    r.route(emb, qs.input_len, qs.expected_out_len, s, mem=hwr.HWR_MEM_HOST, choice=out)
+    assert (out == d["choice"]).all()
