@@ -43,7 +43,7 @@ PROFILE_EVERY = 4              # kernel timing samples one launch in four of eac
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_C5_1Mx256.json")
 KERNEL_NAMES = {   # as the profiler names them
-    "fused": "void hwr::k_route<true, false, false, false, false>(hwr::RouteArgs)",
+    "fused": "void hwr::k_route_stream<false, false, false, false>(hwr::RouteArgs)",
     "mlp": "void hwr::k_mlp_bf16<256, 2, true, 4>(hwr::MlpArgs)",
     "quality": "hwr::k_quality_bf16_lds(hwr::QualityArgs)",
     "gather": "hwr::k_gather(hwr::GatherArgs)",
@@ -194,9 +194,9 @@ def throughput(args, hwr, torch, w, pipeline, steps, warmup):
                              else "once per (query, pair)"},
     )
     if pipeline == "fused":
-        # decisions with the qualities inside, per chunk: embeddings, lengths,
+        # decisions with the qualities inside, all chunks in one launch: embeddings, lengths,
         # N_out and bounds read, choice, feasible and four floats written
-        res["roofline"] = hbm_line(nq * (D * 2 + 12 + 21) + D * 32 * 2, avg("fused"), "k_route", traffic.get("fused"))
+        res["roofline"] = hbm_line(n * (D * 2 + 12 + 21) + D * 32 * 2, avg("fused"), "k_route_stream", traffic.get("fused"))
         # the predictor runs once per (query-feature value, pair) of a step,
         # into the table the decisions read; a batch holds this many values
         feature = np.log(w["il"].cpu().numpy().astype(np.float64)) * 0.125
