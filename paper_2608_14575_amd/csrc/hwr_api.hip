@@ -201,8 +201,8 @@ struct hwr_ctx {
     int nw = 1;                   // cost weights per query (outputs [n][nw] when > 1)
     float w[kMaxWeights] = {};
     // per-pair tables and state
-    int32_t *d_dep_model = nullptr, *d_dep_gpu = nullptr, *d_model_arch = nullptr;
-    float *d_params = nullptr;
+    unsigned char *d_consts = nullptr;   // every constant table and weight below
+    int32_t *d_dep_model = nullptr, *d_dep_gpu = nullptr;
     int32_t *d_pair_arch = nullptr;  // model attributes gathered per pair (single-query path)
     float *d_pair_params = nullptr;
     float *d_dep_f32 = nullptr;
@@ -229,7 +229,7 @@ struct hwr_ctx {
     uint16_t *d_X = nullptr;
     float *d_tab = nullptr, *d_tab_nout = nullptr;   // predictor table [len_rows][table_stride(N)]
     uint16_t *d_len_row = nullptr;    // [kLenBits] feature value (len_index) -> table row
-    uint16_t *d_row_bits = nullptr;   // [len_rows] the values of the bf16 query feature, ascending (same allocation)
+    uint16_t *d_row_bits = nullptr;   // [len_rows] the values of the bf16 query feature, ascending
     int len_rows = 0;
     void *scratch = nullptr;          // this device's static scratch (hwr_route_batch_static)
     // host-memory batches: device staging.  Inputs are double-buffered (the
@@ -310,12 +310,33 @@ hipError_t dev_alloc(T **p, size_t count) {
     return hipMalloc(reinterpret_cast<void **>(p), count * sizeof(T));
 }
 
-template <class T>
-hipError_t upload(T **p, const T *src, size_t count) {
-    hipError_t e = dev_alloc(p, count);
-    if (e != hipSuccess) return e;
-    return hipMemcpy(*p, src, count * sizeof(T), hipMemcpyHostToDevice);
-}
+// A context's constant tables and weights: gathered on the host, then one
+// allocation and one copy for all of them, each 256-byte aligned (seventeen of
+// each took about 0.5 ms longer).
+class Constants {
+  public:
+    template <class T>
+    void add(T **p, const T *src, size_t count) {
+        at_.push_back({reinterpret_cast<void **>(p), bytes_.size()});
+        const unsigned char *s = reinterpret_cast<const unsigned char *>(src);
+        bytes_.insert(bytes_.end(), s, s + count * sizeof(T));
+        bytes_.resize((bytes_.size() + 255) & ~size_t(255));
+    }
+    hipError_t upload(unsigned char **base) {
+        hipError_t e = dev_alloc(base, bytes_.size());
+        if (e == hipSuccess) e = hipMemcpy(*base, bytes_.data(), bytes_.size(), hipMemcpyHostToDevice);
+        for (const auto &a : at_) *a.p = *base + a.off;
+        return e;
+    }
+
+  private:
+    struct At {
+        void **p;
+        size_t off;
+    };
+    std::vector<unsigned char> bytes_;
+    std::vector<At> at_;
+};
 
 bool finite(float v) { return std::isfinite(v); }
 
@@ -641,12 +662,8 @@ void release(hwr_ctx *c) {
     if (c->sstream) (void)hipStreamSynchronize(c->sstream);
     if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
-    void *dev_ptrs[] = {c->d_dep_model, c->d_dep_gpu, c->d_model_arch, c->d_params, c->d_pair_arch,
-                        c->d_pair_params, c->d_dep_f32,
-                        c->d_dep_bf16, c->d_bq, c->d_wq_pk, c->d_wqT, c->d_w1_pk, c->d_w2_pk,
-                        c->d_b1_pk, c->d_b2_pk, c->d_w3_pk, c->d_w3_frag, c->d_wq, c->d_f32, c->d_owner,
-                        c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno, c->d_X, c->d_tab,
-                        c->d_tab_nout, c->d_len_row, c->hin[0].emb, c->hin[0].len, c->hin[0].nout, c->hin[0].slo,
+    void *dev_ptrs[] = {c->d_consts, c->d_dep_f32, c->d_dep_bf16, c->d_owner, c->d_qmat, c->d_ctt, c->d_ctp, c->d_cno,
+                        c->d_X, c->d_tab, c->d_tab_nout, c->hin[0].emb, c->hin[0].len, c->hin[0].nout, c->hin[0].slo,
                         c->hin[1].emb, c->hin[1].len, c->hin[1].nout, c->hin[1].slo, c->d_hchoice,
                         c->d_hval, c->d_hcand, c->d_hqual, c->d_hfeas, c->pack_in, c->pack_emb};
     if (c->cstream) (void)hipStreamSynchronize(c->cstream);
@@ -702,7 +719,7 @@ hwr_status init_impl(const hwr_config *cfg, hwr_ctx **out) {
 // agrees with the kernels' (len_feature) on every value: no feature of a length
 // up to kDense lies within 1e-6 of a bf16 rounding boundary, and both are exact
 // to 1e-14 (tests/test_gpu_table.py checks the values on the device).
-hipError_t init_len_rows(hwr_ctx *c) {
+void init_len_rows(hwr_ctx *c, Constants &consts) {
     constexpr int kDense = 256;
     auto bits = [](int32_t len) { return bf16_rne(static_cast<float>(std::log(static_cast<double>(len)) * 0.125)); };
     std::vector<uint16_t> row_bits, row(kLenBits, 0);
@@ -711,10 +728,8 @@ hipError_t init_len_rows(hwr_ctx *c) {
     for (int b = row_bits.back() + 1; b <= bits(INT32_MAX); ++b) row_bits.push_back(static_cast<uint16_t>(b));
     c->len_rows = static_cast<int>(row_bits.size());
     for (int r = 0; r < c->len_rows; ++r) row[len_index(row_bits[r])] = static_cast<uint16_t>(r);
-    row.insert(row.end(), row_bits.begin(), row_bits.end());   // one upload: the map, then the values
-    const hipError_t e = upload(&c->d_len_row, row.data(), row.size());
-    c->d_row_bits = c->d_len_row + kLenBits;
-    return e;
+    consts.add(&c->d_len_row, row.data(), row.size());
+    consts.add(&c->d_row_bits, row_bits.data(), row_bits.size());
 }
 
 // Fills a new context; on an error it releases it (bail).
@@ -771,11 +786,10 @@ hwr_status init_ctx(hwr_ctx *c, const hwr_config *cfg, const hipDeviceProp_t &pr
         c->scratch = g_scratch_ptr[c->dev];
     }
     const int M = c->M, N = c->N, D = c->D, F = c->F, H = c->H;
-    INIT_HIP(upload(&c->d_dep_model, cfg->dep_model, N));
-    INIT_HIP(upload(&c->d_dep_gpu, cfg->dep_gpu, N));
-    INIT_HIP(upload(&c->d_model_arch, cfg->model_arch, M));
-    INIT_HIP(upload(&c->d_params, cfg->model_params_b, M));
-    INIT_HIP(upload(&c->d_bq, cfg->bq, M));
+    Constants consts;
+    consts.add(&c->d_dep_model, cfg->dep_model, N);
+    consts.add(&c->d_dep_gpu, cfg->dep_gpu, N);
+    consts.add(&c->d_bq, cfg->bq, M);
     {
         std::vector<int32_t> pa(N);
         std::vector<float> pp(N);
@@ -783,36 +797,36 @@ hwr_status init_ctx(hwr_ctx *c, const hwr_config *cfg, const hipDeviceProp_t &pr
             pa[d] = cfg->model_arch[cfg->dep_model[d]];
             pp[d] = cfg->model_params_b[cfg->dep_model[d]];
         }
-        INIT_HIP(upload(&c->d_pair_arch, pa.data(), N));
-        INIT_HIP(upload(&c->d_pair_params, pp.data(), N));
+        consts.add(&c->d_pair_arch, pa.data(), N);
+        consts.add(&c->d_pair_params, pp.data(), N);
     }
     INIT_HIP(dev_alloc(&c->d_dep_f32, static_cast<size_t>(N) * kFeatPad));
     INIT_HIP(dev_alloc(&c->d_dep_bf16, static_cast<size_t>(N) * kFeatPad));
     if (c->bf16) {
         const uint16_t *wq = static_cast<const uint16_t *>(cfg->wq);
         std::vector<uint16_t> wqpk = pack_quality(wq, D, M);
-        INIT_HIP(upload(&c->d_wq_pk, wqpk.data(), wqpk.size()));
+        consts.add(&c->d_wq_pk, wqpk.data(), wqpk.size());
         std::vector<uint16_t> wqT(static_cast<size_t>(M) * D);
         for (int k = 0; k < D; ++k)
             for (int m = 0; m < M; ++m) wqT[static_cast<size_t>(m) * D + k] = wq[static_cast<size_t>(k) * M + m];
-        INIT_HIP(upload(&c->d_wqT, wqT.data(), wqT.size()));
+        consts.add(&c->d_wqT, wqT.data(), wqT.size());
         c->fold_b1 = can_fold_b1(cfg->b1, c->A, c->Gw, H) ? 1 : 0;
         PackedPredictor p = pack_predictor(static_cast<const uint16_t *>(cfg->w1),
                                            static_cast<const uint16_t *>(cfg->w2),
                                            static_cast<const uint16_t *>(cfg->w3), cfg->b1, cfg->b2, F, H,
                                            c->NH, c->fold_b1 != 0);
-        INIT_HIP(upload(&c->d_w1_pk, p.w1.data(), p.w1.size()));
-        INIT_HIP(upload(&c->d_w2_pk, p.w2.data(), p.w2.size()));
-        INIT_HIP(upload(&c->d_b1_pk, p.b1.data(), p.b1.size()));
-        INIT_HIP(upload(&c->d_b2_pk, p.b2.data(), p.b2.size()));
-        INIT_HIP(upload(&c->d_w3_pk, p.w3.data(), p.w3.size()));
-        INIT_HIP(upload(&c->d_w3_frag, p.w3frag.data(), p.w3frag.size()));
+        consts.add(&c->d_w1_pk, p.w1.data(), p.w1.size());
+        consts.add(&c->d_w2_pk, p.w2.data(), p.w2.size());
+        consts.add(&c->d_b1_pk, p.b1.data(), p.b1.size());
+        consts.add(&c->d_b2_pk, p.b2.data(), p.b2.size());
+        consts.add(&c->d_w3_pk, p.w3.data(), p.w3.size());
+        consts.add(&c->d_w3_frag, p.w3frag.data(), p.w3frag.size());
     } else {
         const std::vector<float> wq = pack_quality_f32(static_cast<const float *>(cfg->wq), D, M);
-        INIT_HIP(upload(&c->d_wq, wq.data(), wq.size()));
+        consts.add(&c->d_wq, wq.data(), wq.size());
         c->kq = c->A + c->Gw + 8 <= 16 ? 1 : 2;
         const std::vector<float> p = pack_predictor_f32(cfg, c->kq, c->NH);
-        INIT_HIP(upload(&c->d_f32, p.data(), p.size()));
+        consts.add(&c->d_f32, p.data(), p.size());
         INIT_HIP(dev_alloc(&c->d_owner, kOwnLens));
     }
     const size_t chunk = static_cast<size_t>(c->max_chunk);
@@ -827,11 +841,12 @@ hwr_status init_ctx(hwr_ctx *c, const hwr_config *cfg, const hipDeviceProp_t &pr
     if (c->bf16 && c->pipeline == HWR_PIPE_STAGED) INIT_HIP(dev_alloc(&c->d_X, ldq * N * kFeatPad));
     // predictor table: rows by feature value (fused), by query (fp32)
     if (!c->bf16 || c->pipeline == HWR_PIPE_FUSED) {
-        if (c->bf16) INIT_HIP(init_len_rows(c));
+        if (c->bf16) init_len_rows(c, consts);
         const size_t entries = (c->bf16 ? static_cast<size_t>(c->len_rows) : chunk) * table_stride(N);
         INIT_HIP(dev_alloc(&c->d_tab, entries * 2));
         if (c->NH == 3) INIT_HIP(dev_alloc(&c->d_tab_nout, entries));
     }
+    INIT_HIP(consts.upload(&c->d_consts));
     INIT_HIP(hipHostMalloc(reinterpret_cast<void **>(&c->h_ring),
                            sizeof(hwr_hw_state) * N * kStateSlots, hipHostMallocMapped));
     for (int i = 0; i < kStateSlots; ++i) INIT_HIP(hipEventCreateWithFlags(&c->ring_ev[i], hipEventDisableTiming));
