@@ -1223,17 +1223,6 @@ hwr_status upload_pageable(hwr_ctx *c, void *dst, const void *src, size_t bytes,
     return HWR_OK;
 }
 
-// Grow-only device buffer (idle: every host batch ends with its stream).
-hwr_status grow_dev(hwr_ctx *c, unsigned char **p, size_t *cap, size_t bytes) {
-    if (bytes <= *cap) return HWR_OK;
-    if (*p) (void)hipFree(*p);
-    *p = nullptr;
-    *cap = 0;
-    HWR_HIP(c, hipMalloc(reinterpret_cast<void **>(p), bytes));
-    *cap = bytes;
-    return HWR_OK;
-}
-
 // Layout of the pinned block: inputs, then outputs, each array 256-byte aligned.
 struct HostPack {
     size_t emb = 0, len = 0, nout = 0, slo = 0, inputs = 0, choice = 0, feasible = 0, val[5] = {}, total = 0;
@@ -1268,24 +1257,44 @@ bool packable(const hwr_ctx *c, const hwr_query_batch *q, const hwr_route_result
     return true;
 }
 
+// Grow-only buffer of single-chunk host batches (idle: every host batch ends
+// with its stream).  False when the memory cannot be had: *p is then null.
+template <class Alloc, class Free>
+bool grow(unsigned char **p, size_t *cap, size_t bytes, Alloc alloc, Free release) {
+    if (bytes <= *cap) return true;
+    if (*p) (void)release(*p);
+    *p = nullptr;
+    *cap = 0;
+    if (alloc(reinterpret_cast<void **>(p), bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+        return false;
+    }
+    *cap = bytes;
+    return true;
+}
+
+// The pinned block and the device buffers that a batch of this layout needs.
+// False: one of them cannot be had (the chunk path uses none of them).
+bool pack_buffers(hwr_ctx *c, const HostPack &k, size_t emb_bytes) {
+    auto pinned = [](void **p, size_t n) { return hipHostMalloc(p, n, hipHostMallocMapped); };
+    auto device = [](void **p, size_t n) { return hipMalloc(p, n); };
+    if (k.total > c->pack_cap) c->d_pack = nullptr;
+    if (!grow(&c->h_pack, &c->pack_cap, k.total, pinned, hipHostFree)) return false;
+    if (!c->d_pack && hipHostGetDevicePointer(reinterpret_cast<void **>(&c->d_pack), c->h_pack, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return (k.inputs <= kPackRead || grow(&c->pack_in, &c->pack_in_cap, k.inputs, device, hipFree)) &&
+           (emb_bytes <= kPackEmb || grow(&c->pack_emb, &c->pack_emb_cap, emb_bytes, device, hipFree));
+}
+
+// After pack_buffers.
 hwr_status route_host_packed(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r, const HostPack &k, HostMem em) {
     const size_t n = static_cast<size_t>(q->n), on = n * c->nw;
     const size_t emb_bytes = n * c->D * (c->bf16 ? 2 : 4);
     hipStream_t s = c->stream;
-    if (k.total > c->pack_cap) {
-        if (c->h_pack) (void)hipHostFree(c->h_pack);
-        c->h_pack = c->d_pack = nullptr;
-        c->pack_cap = 0;
-        HWR_HIP(c, hipHostMalloc(reinterpret_cast<void **>(&c->h_pack), k.total, hipHostMallocMapped));
-        HWR_HIP(c, hipHostGetDevicePointer(reinterpret_cast<void **>(&c->d_pack), c->h_pack, 0));
-        c->pack_cap = k.total;
-    }
-    const unsigned char *in = c->d_pack, *emb = nullptr;
-    if (k.inputs > kPackRead) {
-        const hwr_status st = grow_dev(c, &c->pack_in, &c->pack_in_cap, k.inputs);
-        if (st != HWR_OK) return st;
-        in = c->pack_in;
-    }
+    const unsigned char *in = k.inputs > kPackRead ? c->pack_in : c->d_pack, *emb = nullptr;
     unsigned char *h = c->h_pack;
     std::memcpy(h + k.len, q->input_len, n * 4);
     if (c->NH == 2) std::memcpy(h + k.nout, q->expected_out_len, n * 4);
@@ -1296,10 +1305,8 @@ hwr_status route_host_packed(hwr_ctx *c, const hwr_query_batch *q, hwr_route_res
     }
     if (k.inputs > kPackRead) HWR_HIP(c, hipMemcpyAsync(c->pack_in, h, k.inputs, hipMemcpyHostToDevice, s));
     if (!emb) {
-        hwr_status st = grow_dev(c, &c->pack_emb, &c->pack_emb_cap, emb_bytes);
-        if (st != HWR_OK) return st;
         if (emb_bytes >= kPageMinBytes && em == HostMem::kPageable && page_ring(c)) {
-            st = upload_pageable(c, c->pack_emb, q->emb, emb_bytes, s);
+            const hwr_status st = upload_pageable(c, c->pack_emb, q->emb, emb_bytes, s);
             if (st != HWR_OK) return st;
         } else {
             HWR_HIP(c, hipMemcpyAsync(c->pack_emb, q->emb, emb_bytes, hipMemcpyHostToDevice, s));
@@ -1331,7 +1338,8 @@ hwr_status route_host(hwr_ctx *c, const hwr_query_batch *q, hwr_route_result *r)
     const HostMem em = host_mem(q->emb);
     if (em == HostMem::kDevice) return fail(c, HWR_ERR_INVALID_ARG, "HWR_MEM_HOST batch with a device pointer");
     const HostPack k = host_pack(c, q, emb_bytes);
-    const hwr_status st = packable(c, q, r, k) ? route_host_packed(c, q, r, k, em) : route_host_chunks(c, q, r, em);
+    const bool packed = packable(c, q, r, k) && pack_buffers(c, k, emb_bytes);
+    const hwr_status st = packed ? route_host_packed(c, q, r, k, em) : route_host_chunks(c, q, r, em);
     if (st != HWR_OK) {
         // copies may still read the caller's buffers or write its results:
         // let both streams drain before the caller gets control back
