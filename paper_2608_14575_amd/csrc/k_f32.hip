@@ -88,15 +88,18 @@ __device__ __forceinline__ void quality_f32(const QualityArgs &a, int q0, int wa
 }
 
 // With `owner`, each query also claims its length (< kOwnLens): whichever of
-// the chunk's queries of that length is stored last owns it.  No entry is
-// cleared: a length the chunk holds has been written by it.
+// the chunk's queries of that length is stored last owns it.  Many workgroups
+// store to one entry, hence the atomic stores; the entries are read by later
+// kernels only, whose start makes every workgroup see the one that was stored
+// last.  No entry is cleared: a length the chunk holds has been written by it.
 __global__ __launch_bounds__(256) void k_quality_f32(QualityArgs a, const int32_t *input_len, int32_t *owner) {
     __shared__ QualF32Lds s;
     const int q0 = blockIdx.x * kQualF32Q;
     const int q = q0 + static_cast<int>(threadIdx.x);
     if (owner && threadIdx.x < kQualF32Q && q < a.nq) {
         const uint32_t len = static_cast<uint32_t>(input_len[q]);
-        if (len < static_cast<uint32_t>(kOwnLens)) owner[len] = q;
+        if (len < static_cast<uint32_t>(kOwnLens))
+            __hip_atomic_store(owner + len, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     quality_f32(a, q0, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63, s);
 }
