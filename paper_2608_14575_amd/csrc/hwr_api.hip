@@ -1000,7 +1000,7 @@ hwr_status route_fused(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, c
     ta.tab_nout = w.tab_nout;
     RouteArgs ra = route_args(c, qu, qa, oa, w, ctt, ctp, cno);
     ra.len_row = by_value ? c->d_len_row : nullptr;
-    const bool inside = quality_inside(c, cn);
+    const bool inside = by_value && quality_inside(c, cn);   // the form that does so reads rows by value only
     if (inside) {
         if (need_table) HWR_HIP(c, timed(c, HWR_K_MLP, [&] { return launch_table(c->H, ta, c->cus, c->stream); }));
         if (!want_quality) ra.quality.qmat = nullptr;

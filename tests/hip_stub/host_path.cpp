@@ -271,11 +271,26 @@ void growing_batches() {
     g_fail_dev = SIZE_MAX;
 }
 
+// On a device of few compute units, batches that fill it while their table rows
+// are still by query: k_route_stream reads the map of rows by value, so they
+// take the form that does not.
+void few_compute_units() {
+    g_cus = 4;
+    Rig r(64);
+    for (int n : {200, 300}) {
+        check(r.route(n, HWR_MEM_DEVICE) == HWR_OK && launches("k_route") == 1, "one decision launch");
+        check(launches("k_route_stream") == 0 && launches("k_table") == 1, std::to_string(n) + " queries: rows by query");
+    }
+    check(r.route(3000, HWR_MEM_DEVICE) == HWR_OK && launches("k_route_stream") == 1, "rows by value: streamed");
+    g_cus = 256;
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
-const Scenario kScenarios[] = {{"memory_short", memory_short}, {"growing_batches", growing_batches}};
+const Scenario kScenarios[] = {{"memory_short", memory_short}, {"growing_batches", growing_batches},
+                               {"few_compute_units", few_compute_units}};
 
 }  // namespace
 
