@@ -390,6 +390,18 @@ std::vector<float> pack_quality_f32(const float *wq, int D, int M) {
     return out;
 }
 
+// Layer-1 k-steps / 4 of the fp32 predictor: 1 when no feature lies past slot 15.
+// The weights of the slots left out multiply zeros, which adds nothing to a sum as
+// long as they are finite (0 x inf is a NaN).
+int layer1_steps_f32(const hwr_config *cfg) {
+    if (cfg->arch_width + cfg->gpu_width + 8 > 16) return 2;
+    const float *w1 = static_cast<const float *>(cfg->w1);
+    const size_t H = cfg->hidden;
+    for (size_t i = 16 * H; i < cfg->feat_dim * H; ++i)
+        if (!finite(w1[i])) return 2;
+    return 1;
+}
+
 // fp32 predictor, laid out as F32Weights<H>.  Layer 1 A operands: lane (n, g),
 // k-step s holds W1[4 kq g + s][16 rt + n] (zero past F).  Layer 2: lane (n, g)
 // of k tile t, k-step i holds W2[16 t + 4 g + i][16 rt + n].  Heads
@@ -825,7 +837,7 @@ hwr_status init_ctx(hwr_ctx *c, const hwr_config *cfg, const hipDeviceProp_t &pr
     } else {
         const std::vector<float> wq = pack_quality_f32(static_cast<const float *>(cfg->wq), D, M);
         consts.add(&c->d_wq, wq.data(), wq.size());
-        c->kq = c->A + c->Gw + 8 <= 16 ? 1 : 2;
+        c->kq = layer1_steps_f32(cfg);
         const std::vector<float> p = pack_predictor_f32(cfg, c->kq, c->NH);
         consts.add(&c->d_f32, p.data(), p.size());
         INIT_HIP(dev_alloc(&c->d_owner, kOwnLens));

@@ -206,7 +206,7 @@ struct F32Predictor {
 };
 struct MlpF32Args {
     int N, ldn, len_slot, nheads;
-    int kq;                       // layer-1 k-steps / 4: 1 (no feature past slot 15) or 2
+    int kq;                       // layer-1 k-steps / 4: 1 (slots past 15 add nothing) or 2
     QueryArgs q;
     const float *dep_f32;         // [N][32]
     F32Predictor p;

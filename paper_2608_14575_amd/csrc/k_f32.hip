@@ -152,8 +152,8 @@ __device__ __forceinline__ void stage_f32(const F32Predictor &p, F32Weights<H> &
 }
 
 // The candidate features of one lane: k-steps s = 0 .. 4 kq - 1 take feature
-// 4 kq g + s of its candidate (kq = 1 or 2: the features past 16 are all zero
-// or not).
+// 4 kq g + s of its candidate (kq = 1: the slots past 15 are zero and their
+// weights finite).
 struct F32Features {
     f32x4 x[2];
 };

@@ -60,3 +60,25 @@ def test_embeddings_at_any_float_address(n):
     torch.cuda.synchronize()
     for k in out:
         assert out[k].cpu().numpy().tobytes() == ref[k].tobytes(), k
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("n", [30, 1500])
+def test_weights_of_unused_slots(n, value):
+    """Weights of the feature slots past the last signal multiply zeros: an
+    infinite or NaN one makes its hidden unit's sum NaN, which the ReLU takes to
+    0, in the oracle and here, whichever slots a kernel form would skip."""
+    sp = S.spec("C1", n_queries=n)
+    pb, st, qs = S.make_problem(sp, 6), S.make_state(sp, 6), S.make_queries(sp, 6)
+    used = sp.arch_width + sp.gpu_width + 8
+    assert used <= 16 < sp.feat_dim
+    pb.w1[18, 1::4] = value
+    pb.w1[sp.feat_dim - 1, 2::4] = value
+    r = G.make_router(pb)
+    r.update(st)
+    out = G.route_device(r, qs, "f32")
+    r.close()
+    rep = G.check(pb, st, qs, out)
+    print(rep.summary(), flush=True)
+    assert rep.ok, rep.failures[:5]
+    assert rep.max_rel_ttft < 1e-5 and rep.max_rel_tpot < 1e-5
