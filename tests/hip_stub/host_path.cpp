@@ -37,6 +37,7 @@ std::map<char *, size_t> g_dev, g_pinned;
 int g_dev_mallocs = 0, g_pinned_mallocs = 0;
 size_t g_fail_pinned = SIZE_MAX, g_fail_dev = SIZE_MAX;    // allocations of this many bytes or more fail
 int g_cus = 256;
+bool g_busy = false;             // streams have work left
 uintptr_t g_next = 0x1000;
 dim3 g_grid, g_block;
 size_t g_shm;
@@ -151,7 +152,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { return *s = handle<hipStream_t>(), hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return g_busy ? hipErrorNotReady : hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     g_log.push_back({"wait", s, e, 0, ""});
@@ -285,12 +286,42 @@ void few_compute_units() {
     g_cus = 256;
 }
 
+// Embeddings that go up by themselves do so on a stream of their own, beside
+// whatever the context's stream still has to run; the kernels wait for them.
+// With nothing left to run there, they take the context's stream.
+// Both copies: the caller's memory directly, and through the pinned ring.
+void upload_beside_the_stream() {
+    for (int n : {1500, 12000}) {
+        Rig r(768);
+        check(r.route(n) == HWR_OK, "idle");
+        for (const Op &o : g_log) check(o.stream == r.stream && o.what != "wait", "idle: one stream");
+        g_busy = true;
+        for (int call = 0; call < 2; ++call) {
+            check(r.route(n) == HWR_OK, std::to_string(n) + " queries");
+            size_t up = 0, copied = 0;
+            void *upload = nullptr, *event = nullptr;
+            bool waits = false, after = false;
+            for (const Op &o : g_log) {
+                if (o.what == "copy" && o.stream != r.stream) up += o.bytes, upload = o.stream, copied = up;
+                // the event recorded after the whole copy is the one waited for
+                if (o.what == "record" && o.stream == upload && copied == r.emb.size() * 2) event = o.obj;
+                if (o.what == "wait" && o.stream == r.stream && o.obj == event && event) waits = true;
+                if (o.what == "launch" && o.kernel.find("k_state") == std::string::npos) after = after || !waits;
+            }
+            check(up == r.emb.size() * 2, "every byte of the embeddings on the upload stream");
+            check(waits && !after, "the kernels wait for the upload");
+        }
+        g_busy = false;
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {{"memory_short", memory_short}, {"growing_batches", growing_batches},
-                               {"few_compute_units", few_compute_units}};
+                               {"few_compute_units", few_compute_units},
+                               {"upload_beside_the_stream", upload_beside_the_stream}};
 
 }  // namespace
 

@@ -30,7 +30,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["memory_short", "growing_batches", "few_compute_units"])
+@pytest.mark.parametrize("scenario", ["memory_short", "growing_batches", "few_compute_units",
+                                      "upload_beside_the_stream"])
 def test_host_runtime(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
