@@ -187,7 +187,7 @@ struct Rig {
     std::vector<uint8_t> feasible;
     std::vector<float> slo, utility, cand;
 
-    explicit Rig(int d, int max_chunk = 0) : D(d) {
+    explicit Rig(int d, int max_chunk = 0, int weights = 0) : D(d) {
         std::vector<int32_t> dep_model(N), dep_gpu(N), arch(M, 0);
         for (int i = 0; i < N; ++i) dep_model[i] = i % M, dep_gpu[i] = i / M;
         std::vector<float> params(M, 7.0f), zf(static_cast<size_t>(H), 0.0f);
@@ -199,6 +199,8 @@ struct Rig {
         c.dep_model = dep_model.data(), c.dep_gpu = dep_gpu.data(), c.model_arch = arch.data();
         c.model_params_b = params.data(), c.wq = c.w1 = c.w2 = c.w3 = z.data();
         c.bq = c.b1 = c.b2 = c.b3 = zf.data();
+        const std::vector<float> cw(8, 0.5f);
+        c.n_weights = weights, c.cost_weights = cw.data();
         c.stream = handle<void *>();
         check(hwr_init(&c, &ctx) == HWR_OK, "init");
         stream = c.stream;
@@ -315,13 +317,38 @@ void upload_beside_the_stream() {
     }
 }
 
+// Results in device memory are copied there, not written by the host; a block
+// over 8 MB is not pinned.
+void chunk_path_instead() {
+    Rig r(64);
+    void *choice = nullptr;
+    check(hipMalloc(&choice, 300 * 4) == hipSuccess, "result");
+    check(r.route(300) == HWR_OK, "host result");
+    for (const Op &o : g_log) check(o.what != "copy", "host result: no copy");
+    hwr_query_batch q{300, HWR_MEM_HOST, r.emb.data(), r.len.data(), r.nout.data(), r.slo.data()};
+    hwr_route_result res{};
+    res.choice = static_cast<int32_t *>(choice);
+    g_log.clear();
+    check(hwr_route_batch(r.ctx, &q, &res) == HWR_OK, "device result");
+    bool copied = false;
+    for (const Op &o : g_log) copied = copied || (o.what == "copy" && o.obj == choice && o.bytes == 1200);
+    check(copied, "device result: copied");
+    const int pinned = g_pinned_mallocs;
+    Rig w(64, 0, 8);
+    const int own = g_pinned_mallocs - pinned;
+    check(w.route(40000, HWR_MEM_HOST, false, 8) == HWR_OK && g_pinned_mallocs == pinned + own, "block over 8 MB: none pinned");
+    check(w.route(38000, HWR_MEM_HOST, false, 8) == HWR_OK && g_pinned_mallocs == pinned + own + 1, "block under 8 MB");
+    (void)hipFree(choice);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {{"memory_short", memory_short}, {"growing_batches", growing_batches},
                                {"few_compute_units", few_compute_units},
-                               {"upload_beside_the_stream", upload_beside_the_stream}};
+                               {"upload_beside_the_stream", upload_beside_the_stream},
+                               {"chunk_path_instead", chunk_path_instead}};
 
 }  // namespace
 

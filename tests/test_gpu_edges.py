@@ -447,3 +447,46 @@ def test_host_batches_of_one_chunk(dtype, n, kw, slo):
     out = np.full(d["choice"].shape, -1, np.int32)
     r.route(emb, qs.input_len, qs.expected_out_len, s, mem=hwr.HWR_MEM_HOST, choice=out)
     assert (out == d["choice"]).all()
+
+
+@pytest.mark.parametrize("busy", [False, True])
+@pytest.mark.parametrize("pinned", [False, True])
+def test_large_host_batches_of_one_chunk(pinned, busy):
+    """41 MB of embeddings in one chunk: through the pinned ring (pageable) or
+    directly (pinned) into the device buffer of the embeddings, on the context's
+    stream or, with work left on it, on the upload stream; outputs through the
+    pinned block.  Twice, then a smaller batch and the whole one again, against
+    the device path, bit for bit."""
+    import torch
+    sp, pb, st, qs = _case("C3", n_queries=20000)
+    r = G.make_router(pb)
+    r.update(st)
+    d = G.route_device(r, qs, sp.dtype, candidates=False)
+    emb = qs.emb_bits
+    if pinned:
+        emb = torch.from_numpy(np.ascontiguousarray(emb)).pin_memory().numpy()
+    assert emb.nbytes >= 16 << 20
+    a = torch.randn((4096, 4096), device="cuda")
+    for n in (20000, 20000, 700, 20000):
+        if busy:
+            for _ in range(8):
+                a = torch.mm(a, a).clamp_(-1.0, 1.0)
+        h = r.route_host(emb[:n], qs.input_len[:n], qs.expected_out_len[:n], qs.slo_s[:n])
+        _same({k: v[:n] for k, v in d.items()}, h)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n", [38000, 40000])
+def test_host_batches_around_the_largest_pinned_block(n):
+    """Eight cost weights: lengths, bounds and outputs of 38,000 queries (8.06
+    million bytes) fit the 8 MB of the pinned block, those of 40,000 (8.48) do not
+    and the batch takes the chunk path; both give the device path's bits."""
+    block = n * 12 + n * 8 * 25
+    assert (block < 8 << 20) == (n == 38000)
+    sp, pb, st, qs = _case("C2", n_queries=n, embed_dim=64, hidden=64)
+    r = G.make_router(pb, cost_weights=[0.0, 0.1, 0.25, 0.5, 0.75, 1.0, 1.5, 2.0])
+    r.update(st)
+    d = G.route_device(r, qs, sp.dtype, candidates=False)
+    for _ in range(2):
+        h = r.route_host(qs.emb_bits, qs.input_len, qs.expected_out_len, qs.slo_s)
+        _same(d, h)

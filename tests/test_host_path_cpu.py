@@ -31,7 +31,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["memory_short", "growing_batches", "few_compute_units",
-                                      "upload_beside_the_stream"])
+                                      "upload_beside_the_stream", "chunk_path_instead"])
 def test_host_runtime(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
