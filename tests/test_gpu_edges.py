@@ -1,6 +1,6 @@
 """GPU edge cases and invariants of the C ABI: error paths, empty and ragged
-batches, chunking and workgroup-split invariance (bit-exact), fused vs
-staged, host vs device memory, degenerate decisions, maximum sizes."""
+batches, chunking invariance (bit-exact), fused vs staged, host vs device
+memory, degenerate decisions, maximum sizes."""
 import numpy as np
 import pytest
 
@@ -99,17 +99,18 @@ def test_chunking_is_invisible(pipeline, chunk):
 
 @pytest.mark.parametrize("embed_dim", [768, 576])
 def test_quality_unroll_is_invisible(embed_dim):
-    """The quality GEMM has three forms with one MFMA chain order: small
-    grids load four embedding slices ahead (one wave per workgroup); large
-    ones stream rows through LDS when D is a multiple of 256 (768), else load
-    one slice at a time (576).  A batch routed in one large chunk and in
-    small chunks gives bit-identical outputs, Q matrix included."""
+    """The quality kernel of the staged pipeline has three forms with one MFMA
+    chain order (the fused pipeline's own forms are compared with them in
+    test_gpu_table.py): small grids load four embedding slices ahead (one wave
+    per workgroup); large ones stream rows through LDS when D is a multiple of
+    256 (768), else load one slice at a time (576).  A batch routed in one large
+    chunk and in small chunks gives bit-identical outputs, Q matrix included."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     n = 128 * cus + 5                       # one chunk: grid above the CU count
     sp, pb, st, qs = _case(n_queries=n, seed=13, embed_dim=embed_dim)
-    big = G.make_router(pb, max_chunk=n)
-    small = G.make_router(pb, max_chunk=128 * (cus // 2))
+    big = G.make_router(pb, max_chunk=n, pipeline="staged")
+    small = G.make_router(pb, max_chunk=128 * (cus // 2), pipeline="staged")
     big.update(st)
     small.update(st)
     _same(G.route_device(big, qs, "bf16"), G.route_device(small, qs, "bf16"))
@@ -136,10 +137,10 @@ def test_fp32_chunking_is_invisible(kw):
     _same(outs[0], outs[2])
 
 
-def test_fused_equals_staged_and_split_equals_unsplit():
+def test_fused_equals_staged():
     """Same arithmetic per candidate in every mode: bit-identical outputs.
-    40 queries over 64 pairs makes the fused kernel split the pairs over
-    workgroups and merge their keys."""
+    40 queries over 64 pairs at H = 256: the fused table has a row per query and
+    the quality tiles run beside it."""
     sp, pb, st, qs = _case("C3", n_queries=40, seed=12)
     f = G.make_router(pb, pipeline="fused")
     s = G.make_router(pb, pipeline="staged")

@@ -37,15 +37,15 @@ def test_c1_fp32_host_full():
 
 
 @pytest.mark.parametrize("hidden,heads,nq,models,D", [
-    (64, 2, 1, 4, 384),          # one query: one workgroup, one busy wave of the quality kernel
-    (64, 2, 1027, 4, 384),       # 8,216 candidates: waves loop over candidates; ragged workgroups
-    (128, 2, 301, 32, 192),      # H = 128 (two units per lane), 32 models, D = 3 x 64
+    (64, 2, 1, 4, 384),          # one query: one workgroup of each kind
+    (64, 2, 1027, 4, 384),       # 8,216 candidates: rows by distinct length; ragged workgroups
+    (128, 2, 301, 32, 192),      # H = 128, 32 models (two model tiles), D = 3 x 64
     (128, 3, 523, 6, 448),       # three heads: N_out predicted per candidate
 ])
 def test_fp32_device_shapes(hidden, heads, nq, models, D):
-    """fp32 predictor (one wave per candidate) and quality (one wave per
-    query) at shapes past C1: H = 128, three heads, 32 models, batches
-    larger than one pass of the grid, ragged query counts."""
+    """fp32 predictor and quality at shapes past C1: H = 128, three heads, 32
+    models, batches of the small form (every candidate) and of the one that
+    evaluates a row per distinct length, ragged query counts."""
     sp = S.spec("C1", n_queries=nq, hidden=hidden, n_heads=heads, n_models=models, embed_dim=D)
     pb, st, qs = S.make_problem(sp, 11), S.make_state(sp, 11), S.make_queries(sp, 11)
     r = G.make_router(pb)
@@ -93,9 +93,9 @@ def test_c3_shape_ragged_tail(pipeline):
 
 @pytest.mark.parametrize("pipeline", ["fused", "staged"])
 def test_c3_full_size_per_candidate(pipeline):
-    """65,536 queries x 64 pairs in one chunk (fused: 256 workgroups, the
-    unsplit launch; staged: gather, four-tile predictor and epilogue at full
-    size): every prediction and quality of every 16th query compared with the
+    """65,536 queries x 64 pairs in one chunk (fused: predictor table and the
+    streaming decision kernel; staged: gather, four-tile predictor and epilogue
+    at full size): every prediction and quality of every 16th query compared with the
     oracle, and every choice of the sample under the acceptance rule."""
     import torch
     sp = S.spec("C3")
@@ -140,8 +140,8 @@ def _c5_inputs(sp, seed, dev):
 @pytest.mark.parametrize("pipeline", ["fused", "staged"])
 def test_c5_full_size_per_candidate(pipeline):
     """1,048,576 queries x 256 pairs in 65,536-query chunks -- the launch
-    configuration the benchmark times (fused: one unsplit launch per chunk;
-    staged: the staged pipeline's line of the benchmark).  The batch is
+    configuration the benchmark times (fused: the predictor table, then all
+    chunks in one streaming launch; staged: the staged pipeline's line of the benchmark).  The batch is
     routed twice: without per-candidate outputs (the benchmark's kernel form)
     and with them; both give identical decisions.  Every 256th query across
     all 16 chunks (4,096 queries x 256 pairs) is compared with the oracle
@@ -281,21 +281,20 @@ def test_replicate_seeds(name, kw, pipeline, offset):
 
 
 @pytest.mark.parametrize("kw,pipeline", [
-    (dict(), "fused"),                                           # H = 128, lean and non-lean
+    (dict(), "staged"),                                          # H = 128
     (dict(n_heads=3), "staged"),                                 # H = 128, three heads
-    (dict(hidden=256), "staged"),                                # H = 256 staged
-    (dict(hidden=256, n_heads=3), "fused"),                      # H = 256, three heads
-    (dict(score_mode=1, cost_weight=0.3, **S.PAPER_SLO), "fused"),   # H = 128, the paper's rules
+    (dict(hidden=256), "staged"),                                # H = 256
+    (dict(hidden=256, n_heads=3), "staged"),                     # H = 256, three heads
+    (dict(score_mode=1, cost_weight=0.3, **S.PAPER_SLO), "staged"),   # H = 128, the paper's rules
 ])
 def test_four_tile_form_equals_two_tile_form(kw, pipeline):
-    """A chunk that gives every compute unit a workgroup (256 queries each)
-    takes the four-column-tile, one-wave-per-SIMD predictor at H = 128 and
-    256; half that chunk takes the two-tile form (the pair range split over
-    workgroups).  Both give the same bits -- decisions, per-candidate
-    predictions, the Q matrix -- and the four-tile form's decisions are the
-    same with and without per-candidate outputs (its lean and full
-    instantiations).  Every 64th query is also checked against the oracle
-    (Sec. 3.2 Eq. 1-3)."""
+    """Staged predictor: a chunk that gives every compute unit a workgroup (256
+    queries each) takes the four-column-tile, one-wave-per-SIMD form at H = 128
+    and 256; half that chunk takes the two-tile form.  Both give the same bits --
+    decisions, per-candidate predictions, the Q matrix -- and the decisions are
+    the same with and without per-candidate outputs.  Every 64th query is also
+    checked against the oracle (Sec. 3.2 Eq. 1-3).  (The fused pipeline has no
+    such forms; its own are compared with the staged pipeline.)"""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     n = 256 * cus

@@ -56,10 +56,8 @@ def test_every_launch_is_timed_and_results_do_not_change(pipeline, kinds):
         assert ms > 0.0, k
         total += ms
     assert total <= wall_ms, (total, wall_ms)
-    # small chunks may split the pairs over several workgroups and merge them
-    extra = {"state", "merge"} if pipeline == "fused" else {"state"}
-    assert sum(n for k, (_, n) in kt.items() if k not in kinds and k not in extra) == 0
-    assert kt["merge"][1] in (0, 3) and kt["state"][1] <= 1
+    assert sum(n for k, (_, n) in kt.items() if k not in kinds and k != "state") == 0
+    assert kt["state"][1] <= 1
 
 
 def test_sampled_timing_counts_one_launch_in_k():

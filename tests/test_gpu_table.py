@@ -96,8 +96,8 @@ def test_quality_inside_the_decision_kernel(embed_dim, extra):
 @pytest.mark.parametrize("n", [200, 1000, 20000])
 def test_utilities_without_an_order(n):
     """Infinite and NaN embeddings (qualities, utilities) and bounds that only
-    some pairs, or none, meet: the decision kernel's two running bests and
-    their fallbacks."""
+    some pairs, or none, meet: a lane's running best, from its first pair at
+    -inf to a feasible one, in the small and the streaming form."""
     def edit(qs):
         bits = qs.emb_bits
         bits[0::7, 0] = 0x7F80      # inf

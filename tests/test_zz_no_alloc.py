@@ -2,10 +2,10 @@
 space is a static device array of the library) against hwr_route_batch on
 the same context: identical outputs, bit for bit, on two calls in a row, the
 second with fewer queries (and other queries), through the C ABI.  Covers
-the fused predictor in its split (small batch) and unsplit (full chunk)
-launches, three heads, the staged pipeline in several scratch-sized chunks,
-several cost weights, and the fp32 path; no device memory is allocated
-during the calls; host batches are refused."""
+the fused pipeline with the quality tiles beside the predictor table (small
+batches) and with the streaming decision kernel, three heads, the staged
+pipeline in several scratch-sized chunks, several cost weights, and the fp32
+path; no device memory is allocated during the calls; host batches are refused."""
 import numpy as np
 import pytest
 
@@ -27,8 +27,8 @@ def _device():
 
 CASES = [
     # (config, overrides, router keywords, first and second batch sizes)
-    ("C2", dict(), dict(), 3000, 700),                          # fused, split launches
-    ("C3", dict(n_queries=65536), dict(), 65536, 40000),        # fused H = 256, unsplit four-tile launch
+    ("C2", dict(), dict(), 3000, 700),                          # fused: table and quality tiles, then decisions
+    ("C3", dict(n_queries=65536), dict(), 65536, 40000),        # fused H = 256: table, then the streaming kernel
     ("C2", dict(n_heads=3), dict(), 1500, 333),                 # three heads
     ("C5", dict(n_queries=5000), dict(pipeline="staged"), 5000, 1234),   # staged: chunks of the scratch
     ("C2", dict(), dict(cost_weights=[0.0, 0.5, 2.0]), 1200, 200),        # several cost weights
