@@ -53,12 +53,17 @@
  *  - HWR_MEM_DEVICE batches are ordered on the context's stream and return
  *    without waiting; HWR_MEM_HOST batches return with the results written.
  *    A host batch of at most max_chunk queries without per-candidate outputs
- *    passes through pinned memory of the context (grown on demand, up to 8 MB,
- *    held until hwr_free); a larger one is streamed: the next chunk's upload
- *    (on a second stream of the context) overlaps this chunk's kernels.  A
+ *    passes through a pinned block of the context (256 KB, doubled on demand up
+ *    to 8 MB); more than 1 MB of embeddings, or of inputs, goes up into device
+ *    buffers of the context that grow the same way, to max_chunk * D embedding
+ *    elements at most (beside work still enqueued on the context's stream, on a
+ *    second stream of the context).  Every other host batch -- more queries,
+ *    per-candidate outputs, lengths and results of over 8 MB, results in device
+ *    memory, or no memory for those buffers -- is streamed in chunks: the next
+ *    chunk's upload, on the second stream, overlaps this chunk's kernels.  A
  *    host batch in pageable memory with 16 MB of embeddings or more is copied
  *    through 32 MB of pinned memory the context allocates on first use, by
- *    up to seven host threads of its own (held until hwr_free).
+ *    up to seven host threads of its own.  All of it is held until hwr_free.
  *  - A context is not thread-safe: one context per thread (or per stream).
  */
 #ifndef HWR_H
@@ -235,14 +240,14 @@ hwr_status hwr_route_batch(hwr_ctx *ctx, const hwr_query_batch *q, hwr_route_res
  * forbid hipMalloc.  Same arguments, results and ordering as hwr_route_batch
  * for HWR_MEM_DEVICE batches, bit for bit; it calls no hipMalloc, hipFree or
  * other allocating routine (and creates no events: kernel timing is skipped).
- * Its work space -- the quality matrix, the predictor table and, for staged and
- * fp32 contexts, the per-candidate predictions and features -- lives in a static 64 MiB device array of the library, one per
- * GPU, held until the process ends (its address is taken by the first
- * hwr_init on each device).  A batch is routed in chunks of as many queries
- * as that space holds (at most max_chunk); HWR_ERR_UNSUPPORTED when a single
- * query needs more than 64 MiB (about 3,600 pairs at most, staged).  Host
- * batches: HWR_ERR_INVALID_ARG (they stage through buffers allocated on first
- * use).  Every call on one GPU uses that GPU's one array, from any context:
+ * Its work space -- the quality matrix, the predictor table and, for staged
+ * contexts, the per-candidate predictions and features -- lives in a static
+ * 64 MiB device array of the library, one per GPU, held until the process ends
+ * (its address is taken by the first hwr_init on each device).  A batch is
+ * routed in chunks of as many queries as that space holds (at most max_chunk);
+ * HWR_ERR_UNSUPPORTED when a single query needs more than 64 MiB (no supported
+ * shape does).  Host batches: HWR_ERR_INVALID_ARG (they stage through buffers
+ * allocated on first use).  Every call on one GPU uses that GPU's one array, from any context:
  * calls that overlap in time on one GPU (different streams, threads or
  * contexts) race on it and give undefined results; calls ordered on one
  * stream do not.  Each call writes every element it later reads; nothing

@@ -55,7 +55,6 @@ struct Workspace {
     float *ctt = nullptr, *ctp = nullptr, *cno = nullptr;
     uint16_t *X = nullptr;
     int max_chunk = 0;
-    bool timing = true;             // kernel timing allowed (it may create events)
 };
 
 // Scratch of the entry point that allocates nothing (hwr_route_batch_static):
@@ -987,15 +986,22 @@ hwr_status route_f32(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, con
     return HWR_OK;
 }
 
-// Whether a chunk of the fused pipeline gives every compute unit a 64-query
-// workgroup of the decision kernel, which then computes the qualities itself.
+// Whether a chunk of the fused pipeline has 64 queries per compute unit, from
+// where on the decision kernel computes the qualities itself.  The streaming
+// kernel's workgroups hold 128 queries, so every compute unit has one from twice
+// that size on.  Both forms, in us at 256 compute units (table with the quality
+// tiles, then decisions | table, then streaming): 32 pairs, D = 768, H = 128:
+// 16,321 queries 15.9 | 20.1, 24,576 19.9 | 20.4, 32,641 23.2 | 20.9, 65,536 30.9 |
+// 27.2; 256 pairs, D = 1,536, H = 256: 27.9 | 45.0, 33.9 | 45.9, 40.8 | 47.0, 63.2 |
+// 61.8; 8 pairs, D = 256, H = 64: 11.1 | 13.2, 12.0 | 13.3, 12.7 | 13.4, 18.4 | 15.2.
+// So the streaming form is the better one from about 25,000 queries (few pairs,
+// ordinary D) to 36,000 (many) on, and always where it saves chunks.
 bool quality_inside(const hwr_ctx *c, int cn) { return (cn + 63) / 64 >= c->cus; }
 
-// One chunk of the fused pipeline.  Chunks that give every compute unit a
-// 64-query workgroup compute the qualities inside the decision kernel, which
-// streams the embeddings at the rate of a quality kernel alone and hides the
-// decisions under other workgroups' loads; smaller chunks run the quality tiles
-// beside the predictor table, in the same launch, and the decisions after it.
+// One chunk of the fused pipeline.  Chunks of 64 queries per compute unit or more
+// compute the qualities inside the decision kernel (k_route_stream); smaller
+// chunks run the quality tiles beside the predictor table, in the same launch, and
+// the decisions after it (quality_inside).
 hwr_status route_fused(hwr_ctx *c, const QualityArgs &qu, const QueryArgs &qa, const OutArgs &oa, const Workspace &w,
                        bool by_value, bool need_table, float *ctt, float *ctp, float *cno, bool want_quality) {
     const int cn = qa.nq;
@@ -1650,7 +1656,6 @@ hwr_status check_route_args(hwr_ctx *c, const hwr_query_batch *q, const hwr_rout
 // queries as fit, at most max_chunk; 0 rows: one query does not fit.
 Workspace scratch_workspace(const hwr_ctx *c) {
     Workspace w;
-    w.timing = false;
     const size_t M = c->M, N = c->N;
     const bool fused = c->bf16 && c->pipeline == HWR_PIPE_FUSED;
     const bool staged = c->bf16 && c->pipeline == HWR_PIPE_STAGED;

@@ -295,7 +295,6 @@ __device__ inline uint64_t group_max_u64(uint64_t k, int G) {
 
 __device__ inline void write_outputs(const OutArgs &o, int q, uint64_t key, float u,
                                      float e2e, float ttft, float tpot, float nout) {
-    if (!o.choice) return;        // decisions taken by a later kernel
     o.choice[q] = key_pair(key);
     if (o.feasible) o.feasible[q] = key_feasible(key) ? 1 : 0;
     if (o.utility) o.utility[q] = u;

@@ -14,10 +14,8 @@ namespace hwr {
 
 constexpr int kFeatPad = 32;     // feature slots padded to two 16-wide MFMA k-blocks
 constexpr int kQualTile = 32;    // quality GEMM: models padded to one 32-wide tile
-constexpr int kBlock = 256;      // threads per workgroup of the batch kernels
 constexpr int kQPerWave = 64;    // staged predictor: queries per wave in the two-tile form
 constexpr int kQPerBlock = kQPerWave * 4;   // four query sub-blocks per workgroup
-constexpr int kMlpThreads = 512;             // predictor workgroup with two column tiles per wave: 8 waves
 constexpr int kGatherQ = 256;    // feature gather: queries per workgroup (one wave per SIMD)
 constexpr int kMaxPairs = 1024;
 constexpr int kMaxModels = 32;

@@ -292,10 +292,12 @@ __global__ __launch_bounds__(256) void k_mlp_f32_small(MlpF32Args a) {
 // evaluated, and every other query reads its owner's row.  A workgroup lists
 // the owners among up to kF32List queries; the workgroups of one range (grid y)
 // share its (owner, pair) candidates, 32 at a time to a wave, in two 16-column
-// tiles: wide ranges keep the shares even where few queries own a length.  Two
-// column tiles x two k halves give four independent MFMA chains.  8,192 x 24,
-// H = 128 (1,933 lengths): 597 us (one wave per candidate, hidden units
-// broadcast with readlane) -> 26.5 us, two steps of 576 MFMAs per SIMD.
+// tiles.  Two column tiles x two k halves give four independent MFMA chains.
+// 8,192 x 24, H = 128 (1,933 lengths): 597 us (one wave per candidate, hidden
+// units broadcast with readlane) -> 26.5 us, two steps of 576 MFMAs per SIMD.
+// Nothing evens out the owners per range: 99 to 144 at 8,192 queries, 4 to 201,
+// 30 on average, at 65,536 (3,877 lengths, two workgroups to a range), where the
+// fullest range sets the time.
 constexpr int kF32Waves = 8;
 constexpr int kF32List = 512;                     // queries looked through at once
 template <int H, int KQ>

@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_route(RouteArgs a) {
         write_decision<PN>(a, q0 * nw + i, s_key[i], s_row[MULTI ? i / nw : i], s_nout[MULTI ? i / nw : i]);
 }
 
-// LDS of one wave of k_route_stream: the slice being multiplied (64 k of its 32
+// LDS of one wave of k_route_stream: the stage being multiplied (128 k of its 32
 // queries) and, once the qualities are done, the qualities; then the queries'
 // inputs and decision keys.
 constexpr int kStreamSlices = 2;                  // 64-wide slices of k per stage
@@ -274,25 +274,26 @@ __device__ __forceinline__ void wave_sync() {
 constexpr int kStreamWaves = kRouteThreads / 64;
 constexpr int kStreamBlocks = 3;                  // workgroups per compute unit
 
-// Qualities and decisions of a batch that fills the device.  Every wave takes
-// 32 queries at a time by itself, no workgroup barrier: it streams their
-// embeddings through its own LDS in stages of 128 k (the next stage's loads in
-// registers), multiplies them as quality_tile does (same bits), and decides
-// them while the other waves of its SIMD keep loads in flight.  The quality
-// weights come from L2 one stage ahead too: loads return in order, so weights
-// requested behind the next stage's embeddings would wait for memory.
+// Qualities and decisions of a large batch.  Every wave takes 32 queries at a time
+// by itself, no workgroup barrier: it streams their embeddings through its own LDS
+// in stages of 128 k (the next stage's loads in registers), multiplies them as
+// quality_tile does (same bits), and decides them while the other waves of its
+// SIMD keep loads in flight (at 256 compute units a SIMD has one wave up to 32,768
+// queries and three from 98,304 on).  The quality weights come from L2 one stage
+// ahead too: loads return in order, so weights requested behind the next stage's
+// embeddings would wait for memory.
 //
-// Bound by HBM with the decisions' vector instructions beside it.  Measured at
-// 1,048,576 x 256, D = 1,536 (3.25 GB, table included): 709 us; without the
-// decisions 602, the decisions alone about 200.  Workgroups of four waves on
-// 64 queries in 65,536-query launches, with barriers per 256 k, took 884 us (712
-// in one launch with the present decisions); at 65,536 x 64, D = 1,024, 37.6
-// against 46.3 us, and at 30,011 x 60, D = 768, 20.0 against 23.6.  Other
-// shapes, in us for 1M x 256: stages of 64 k with two ahead 739, of 256 k at two
-// waves per SIMD 706 (20.8 at 30,011), four waves per SIMD 739; the next tile's
-// first stage requested before the decisions: no gain.  Non-temporal
-// embedding loads (each byte is read once, and the table stays in L2) took
-// 65,536 x 64 from 43.9 to 39.4 us.
+// Bound by HBM with the decisions' vector instructions beside it, and by the
+// weights' way from L2, which every wave asks for again (2.9 GB at 1M x 256 beside
+// 3.2 GB of embeddings).  Calls at 1,048,576 x 256, D = 1,536 (3.25 GB, table
+// included): 704 us; without the decisions 602, the decisions alone about 200.
+// Workgroups of four waves on 64 queries in 65,536-query launches, with barriers
+// per 256 k, took 884 us (712 in one launch with the present decisions); at 65,536
+// x 64, D = 1,024, 38 against 46 us.  Other shapes, in us for 1M x 256: stages of
+// 64 k with two ahead 739, of 256 k at two waves per SIMD 706, four waves per SIMD
+// 739; the next tile's first stage requested before the decisions: no gain.
+// Non-temporal embedding loads (each byte is read once, and the table stays in L2)
+// took 65,536 x 64 from 43.9 to 39.4 us.
 template <bool PN, bool MULTI, bool GEN, bool DBG>
 __global__ __launch_bounds__(kRouteThreads, kStreamBlocks) void k_route_stream(RouteArgs a) {
     constexpr int NW = MULTI ? kMaxWeights : 1;
