@@ -1,8 +1,9 @@
 """Benchmark: batched routing-score evaluation on one MI355X.
 
 Step = one call of hwr_route_batch over the whole throughput workload
-(1,048,576 queries x 256 model-GPU pairs, 16 chunks of 65,536 queries on one
-stream, inputs resident in HBM).  Prints one JSON line with candidates
+(1,048,576 queries x 256 model-GPU pairs, max_chunk 65,536, on one stream,
+inputs resident in HBM; the fused pipeline routes the 16 chunks in one launch,
+the staged one one by one).  Prints one JSON line with candidates
 scored per second, the roofline position of the dominant kernel (quality and
 decisions, HBM-bound; in the staged pipeline the predictor, MFMA-bound)
 measured with HIP events on the launch stream, the

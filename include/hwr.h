@@ -268,7 +268,7 @@ const char *hwr_last_error(const hwr_ctx *ctx);
  * inside the quality launch (HWR_K_QUALITY) on small chunks; chunks of 64
  * queries per compute unit or more compute the qualities inside the decision
  * kernel instead (no HWR_K_QUALITY), all chunks of the batch in one launch, and
- * the table is HWR_K_MLP.  fp32 chunks
+ * the table is HWR_K_MLP.  fp32 decisions are HWR_K_EPILOGUE; fp32 chunks
  * small enough for the predictor and the quality rows to share the device run
  * both in the predictor's launch: HWR_K_MLP, no HWR_K_QUALITY.  HWR_K_MERGE is
  * kept for its index; no kernel reports it.

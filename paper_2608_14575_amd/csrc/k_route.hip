@@ -1,4 +1,4 @@
-// Decisions of the fused pipeline (gfx950): per query, cost (Eq. 2), bound test
+// Decisions of the fused pipeline and of the fp32 path (gfx950): per query, cost (Eq. 2), bound test
 // and utility of every pair from the query's row of the predictor table, then
 // the Eq. 3 argmax, once per cost weight.
 #include <algorithm>
